@@ -11,9 +11,9 @@
 //    chunk) assignment applies an XOR swizzle (chunk ^ ((row >> 1) & 7)) that
 //    spreads the MFMA operand reads -- 32 rows at one k offset, 16 lanes per
 //    LDS cycle over 64 banks -- without conflicts.
-//  * ST LDS stages of 64 k (two for full launches, three for the small-tile
-//    path of latency-bound ones): tile k+ST-1 streams in while tile k is
-//    consumed.  The DMA is issued from inline assembly so the compiler does
+//  * ST LDS stages of 64 k: tile k+ST-1 streams in while tile k is consumed
+//    (launches of about one tile per CU run the deep-pipelined kernel below
+//    instead).  The DMA is issued from inline assembly so the compiler does
 //    not serialise it against the LDS reads; completion is tracked with
 //    explicit s_waitcnt vmcnt and one workgroup barrier per k-step.
 //  * v_mfma_f32_32x32x16_bf16, each wave a (BM/WGM) x (BN/WGN) sub-tile of
@@ -325,6 +325,309 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_tile_kernel(GemmArgs
     }
     wait_lds();
     __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// ---- deep-pipelined per-tile kernel (launches of one or two tiles per CU) ----
+//
+// Small micro-batches give a GEMM about one tile per CU, so nothing overlaps a
+// tile's prologue, k-loop and epilogue but the tile itself, and the k-loop is bound
+// by the DMA into the CU: 105 B/ns of 128-byte row pieces with the operands in the
+// other units' reach (a DMA-only copy of the loop), 0.155 us per 64-wide step of a
+// 64 x 64 tile against 0.07 us for its MFMAs or its LDS reads alone.  Against the
+// per-tile kernel above (0.29 us per step there):
+//  * a whole step's fragments are kept in registers, each 16-wide slice refilled
+//    from the next step's stage right after its MFMAs, so an LDS read has three
+//    slices (seven with KS = 2) to return in; a stage is free one step later, and
+//    the barrier that frees it also publishes the next one;
+//  * a step's DMA instructions are spread over its slices: issued in one block they
+//    hold up the MFMAs behind a full vector memory queue (128 x 128 tiles: 8%);
+//  * 64 x 64 tiles step by 128 k (KS = 2): half the barriers (0.22 -> 0.18 us per 64 k);
+//  * bias, residual and positions are fetched before the first operands, and the
+//    epilogue writes whole 128-byte rows through LDS (1.0 - 1.5 us per launch).
+// One image (577 rows): O-projection 9.6 -> 6.9 us, FC2 23.4 -> 15.8, QKV 11.5 ->
+// 9.4, FC1 14.9 -> 12.0; five images' O-projection 17.7 -> 14.0, FC2 41.5 -> 33.2
+// (back-to-back launches, weights changing).  What is left over the DMA time is
+// 2.3 us of dispatch per launch, about 1 us until the first operands land, and the
+// output.  Same products in the same order as the kernel above, so the same bits.
+template <int BM, int BN, int WGM, int WGN, int ST, int KS>
+struct DCfg : Cfg<BM, BN, WGM, WGN> {
+  using B = Cfg<BM, BN, WGM, WGN>;
+  static constexpr int NH = KS * BK / 16;                       // 16-wide k slices per step
+  static constexpr int STAGE = KS * (B::TA + B::TB), DPS = KS * (B::DA + B::DB);
+  static constexpr int LDS = ST * STAGE;
+  static_assert(ST >= 3, "one stage is read, one may be refilled, one lands");
+  static constexpr int SLAB = 32 * B::WN * 2 > 4096 ? 32 * B::WN * 2 : 4096;   // per-wave epilogue staging
+  static_assert(DPS * (ST - 1) < 64 && LDS <= 160 * 1024 && B::NW * SLAB <= LDS, "vmcnt and LDS range");
+};
+
+template <int BM, int BN, int WGM, int WGN, int ST, int KS, int OUTF32>
+__global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_deep_kernel(GemmArgs a) {
+  using C = DCfg<BM, BN, WGM, WGN, ST, KS>;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) char*)smem);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WGN, wn = wave % WGN;
+  int mi, ni;
+  tile_coords(xcd_tile(blockIdx.x, gridDim.x), (a.M + BM - 1) / BM, (a.N + BN - 1) / BN, mi, ni);
+  const int m0 = mi * BM, n0 = ni * BN;
+  const int KT = a.K / (KS * BK);   // steps
+  const bf16* A = static_cast<const bf16*>(a.A);
+  const bf16* B = static_cast<const bf16*>(a.B);
+
+  unsigned a_off[C::DA], b_off[C::DB];
+  {
+    const int rr = lane / C::CPR, pch = lane % C::CPR;
+#pragma unroll
+    for (int j = 0; j < C::DA; ++j) {
+      const int r = (wave * C::DA + j) * C::RPI + rr;
+      a_off[j] = (unsigned)(((long)min(m0 + r, a.M - 1) * a.lda + (pch ^ C::sw(r)) * 8) * 2);
+    }
+#pragma unroll
+    for (int j = 0; j < C::DB; ++j) {
+      const int r = (wave * C::DB + j) * C::RPI + rr;
+      int gn = min(n0 + r, a.N - 1);
+      if (a.rope_pos) gn = rope_src_row(gn, a.rope_hd, a.rope_hd_inv, a.rope_cols);
+      b_off[j] = (unsigned)(((long)gn * a.ldb + (pch ^ C::sw(r)) * 8) * 2);
+    }
+  }
+  // DMA instructions [d0, d1) of the DPS that fill stage st with step kt's operands
+  auto issue = [&](int kt, int st, int d0, int d1) {
+    const unsigned base = lds0 + st * C::STAGE;
+#pragma unroll
+    for (int d = 0; d < C::DPS; ++d) {
+      if (d < d0 || d >= d1) continue;
+      const int sub = d / (C::DA + C::DB), j = d % (C::DA + C::DB);
+      const unsigned sb = base + sub * (C::TA + C::TB);
+      const int k = (kt * KS + sub) * BK;
+      if (j < C::DA) dma16(sb + (wave * C::DA + j) * 1024, a_off[j < C::DA ? j : 0], A + k);
+      else dma16(sb + C::TA + (wave * C::DB + j - C::DA) * 1024, b_off[j < C::DA ? 0 : j - C::DA], B + k);
+    }
+  };
+  const int lrow = lane & 31, g = lane >> 5, swz = C::sw(lrow);
+  const int a_row = (wm * C::WM + lrow) * BK * 2, b_row = (wn * C::WN + lrow) * BK * 2;
+  constexpr int NH = C::NH;
+  int cofs[BK / 16];
+#pragma unroll
+  for (int h = 0; h < BK / 16; ++h) cofs[h] = ((2 * h + g) ^ swz) << 4;
+  f32x16 acc[C::FM][C::FN];
+#pragma unroll
+  for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+
+  bf16x8 fa[NH][C::FM], fb[NH][C::FN];
+  auto load_slice = [&](int st, int h) {
+    const char* As = smem + st * C::STAGE + h / (BK / 16) * (C::TA + C::TB);
+    const char* Bs = As + C::TA;
+    const int co = cofs[h % (BK / 16)];
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i) fa[h][i] = *reinterpret_cast<const bf16x8*>(As + a_row + i * 32 * BK * 2 + co);
+#pragma unroll
+    for (int j = 0; j < C::FN; ++j) fb[h][j] = *reinterpret_cast<const bf16x8*>(Bs + b_row + j * 32 * BK * 2 + co);
+  };
+  auto mma = [&](int h) {
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+      for (int j = 0; j < C::FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[h][j], fa[h][i], acc[i][j], 0, 0, 0);
+  };
+  auto interleave = [&]() {
+    constexpr int NR = C::FM + C::FN, NM = C::FM * C::FN, NP = NR < NM ? NR : NM;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    if constexpr (NM > NP) __builtin_amdgcn_sched_group_barrier(0x008, NM - NP, 0);
+    if constexpr (NR > NP) __builtin_amdgcn_sched_group_barrier(0x100, NR - NP, 0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // What the epilogue reads besides the sums is fetched before the operands (it
+  // lands first): the lane's bias values and, with a residual, its values of
+  // every block.  Ordinary loads, which the compiler waits for by itself at
+  // their use; by then no DMA is in flight.  Columns past N are clamped or out
+  // of the buffer's range, rows past M out of range.
+  const int rows = min(BM, a.M - m0);
+  const int prow = lane >> 3, pc = (lane & 7) * 4;   // fp32: eight lanes a 128-byte row of a 32 x 32 block
+  uint2 bq[C::FN][OUTF32 ? 1 : 4];
+  u32x4 rq[C::FM * C::FN][4];
+  int4 rp[C::FM];
+  auto out_off = [&](int i, int j, int ld) {   // byte offset of the lane's first row in block (i, j), fp32
+    const int n = n0 + wn * C::WN + j * 32 + pc;
+    return n < a.N ? (unsigned)(((wm * C::WM + i * 32 + prow) * ld + n) * 4) : 0x80000000u;
+  };
+#pragma unroll
+  for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+    for (int q = 0; q < (OUTF32 ? 1 : 4); ++q) {
+      const int n = n0 + wn * C::WN + j * 32 + (OUTF32 ? pc : 8 * q + 4 * g);
+      bq[j][q] = a.bias ? *reinterpret_cast<const uint2*>(static_cast<const bf16*>(a.bias) + min(n, a.N - 4))
+                        : make_uint2(0u, 0u);
+    }
+  if constexpr (OUTF32) {
+    if (a.resid) {
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<float*>(a.resid) + (size_t)m0 * a.ldr, 0, rows * a.ldr * 4, 0x00020000);
+#pragma unroll
+      for (int b = 0; b < C::FM * C::FN; ++b)
+#pragma unroll
+        for (int p = 0; p < 4; ++p)
+          rq[b][p] = __builtin_amdgcn_raw_buffer_load_b128(
+              rs, out_off(b / C::FN, b % C::FN, a.ldr) + (unsigned)(p * 8 * a.ldr * 4), 0, 0);
+    }
+  } else if (a.rope_pos) {
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i) rp[i] = a.rope_pos[min(m0 + wm * C::WM + i * 32 + lrow, a.M - 1)];
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int s = 0; s < ST; ++s)
+    if (s < KT) issue(s, s, 0, C::DPS);
+  wait_tiles<C::DPS, ST - 1>(min(ST, KT) - 1);
+  __builtin_amdgcn_s_barrier();
+#pragma unroll
+  for (int h = 0; h < NH - 1; ++h) load_slice(0, h);
+  int st = 0, pst = ST - 1;   // stages of steps kt and kt - 1
+  for (int kt = 0; kt < KT - 1; ++kt) {
+    // step kt+1 has landed once only the steps after it (up to kt+ST-2) are in flight
+    if (kt == 0) wait_tiles<C::DPS, ST - 2>(min(ST - 2, KT - 2));
+    else wait_tiles<C::DPS, ST - 3>(min(ST - 3, KT - 2 - kt));
+    __builtin_amdgcn_s_barrier();
+    const bool more = kt > 0 && kt - 1 + ST < KT;
+    const int nst = st + 1 == ST ? 0 : st + 1;
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      if (more) issue(kt - 1 + ST, pst, C::DPS * h / NH, C::DPS * (h + 1) / NH);
+      __builtin_amdgcn_sched_barrier(0);
+      if (h == 0) load_slice(st, NH - 1);
+      else load_slice(nst, h - 1);
+      mma(h);
+      interleave();
+    }
+    pst = st;
+    st = nst;
+  }
+  load_slice(st, NH - 1);
+#pragma unroll
+  for (int h = 0; h < NH; ++h) mma(h);
+
+  // ---- epilogue: every wave through its own slab of the operand stages ----
+  wait_lds();
+  __builtin_amdgcn_s_barrier();   // every wave has read its last operands
+  char* slab = smem + wave * C::SLAB;
+  const int es = OUTF32 ? 4 : 2, act = a.act;
+  const __amdgpu_buffer_rsrc_t os = __builtin_amdgcn_make_buffer_rsrc(
+      static_cast<char*>(a.out) + (size_t)m0 * a.ldo * es, 0, rows * a.ldo * es, 0x00020000);
+  if constexpr (OUTF32) {
+    // acc element 4q + e sits at row lrow, column 8q + 4g + e of the block
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i)
+#pragma unroll
+      for (int j = 0; j < C::FN; ++j) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          *reinterpret_cast<float4*>(slab + lrow * 128 + (((2 * q + g) ^ swz) << 4)) =
+              make_float4(acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
+        union { uint2 u; bf16 h[4]; } bb;
+        bb.u = bq[j][0];
+        wait_lds();
+        const unsigned st0 = out_off(i, j, a.ldo);
+#pragma unroll
+        for (int p = 0; p < 4; ++p) {
+          const int r = p * 8 + prow;   // row within the block
+          const float4 s4 = *reinterpret_cast<const float4*>(slab + r * 128 + (((pc >> 2) ^ C::sw(r)) << 4));
+          float v[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] += (float)bb.h[e];
+          if (act == ACT_GELU) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
+          } else if (act == ACT_QUICKGELU) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = quick_gelu(v[e]);
+          }
+          if (a.pos) {
+            const int m = min(m0 + wm * C::WM + i * 32 + r, a.M - 1);
+            const int n = min(n0 + wn * C::WN + j * 32 + pc, a.N - 4);
+            const long pi = (long)(a.pos_idx ? a.pos_idx[m] : m % a.pos_period) * a.ld_pos + n;
+            if (a.pos_f32) {
+              const float4 t = *reinterpret_cast<const float4*>(static_cast<const float*>(a.pos) + pi);
+              v[0] += t.x; v[1] += t.y; v[2] += t.z; v[3] += t.w;
+            } else {
+              union { uint2 u; bf16 h[4]; } t;
+              t.u = *reinterpret_cast<const uint2*>(static_cast<const bf16*>(a.pos) + pi);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) v[e] += (float)t.h[e];
+            }
+          }
+          if (a.resid) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] += __uint_as_float(rq[i * C::FN + j][p][e]);
+          }
+          __builtin_amdgcn_raw_buffer_store_b128(
+              (u32x4){__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])}, os,
+              st0 + (unsigned)(p * 8 * a.ldo * 4), 0, 0);
+        }
+        wait_lds();   // the reads are done before the next block overwrites the slab
+      }
+  } else {
+    // bias, activation and rotation on the sums in place, then whole rows of 32 x WN
+    // bf16 through the slab; the 16-byte chunks of a row are swizzled so that 16
+    // rows' 8-byte writes fall on distinct banks
+    constexpr int RS = C::WN * 2, CH = RS / 16, RPB = 256 / RS, RST = 64 / CH;
+#pragma unroll
+    for (int i = 0; i < C::FM; ++i) {
+#pragma unroll
+      for (int j = 0; j < C::FN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          union { uint2 u; bf16 h[4]; } bb, pk;
+          bb.u = bq[j][q];
+          float v[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = acc[i][j][4 * q + e] + (float)bb.h[e];
+          if (act == ACT_GELU) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = gelu_erf(v[e]);
+          } else if (act == ACT_QUICKGELU) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = quick_gelu(v[e]);
+          }
+          if (a.rope_pos) {   // two interleaved pairs
+            const int n = n0 + wn * C::WN + j * 32 + 8 * q + 4 * g;
+            if (n < a.rope_cols) {
+              const int i0 = rope_in_head(n, a.rope_hd, a.rope_hd_inv) >> 1;
+              rope_rotate(v[0], v[1], rope_turns(a, i0, rp[i].x, rp[i].y, rp[i].z));
+              rope_rotate(v[2], v[3], rope_turns(a, i0 + 1, rp[i].x, rp[i].y, rp[i].z));
+            }
+          }
+if (a.resid) {   // one launch a call (a CLS model's last layer with bf16 output)
+            const long ri = (long)min(m0 + wm * C::WM + i * 32 + lrow, a.M - 1) * a.ldr;
+            const int n = min(n0 + wn * C::WN + j * 32 + 8 * q + 4 * g, a.N - 4);
+            const float4 t = *reinterpret_cast<const float4*>(a.resid + ri + n);
+            v[0] += t.x; v[1] += t.y; v[2] += t.z; v[3] += t.w;
+          }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) pk.h[e] = (bf16)v[e];
+          *reinterpret_cast<uint2*>(slab + lrow * RS + (((4 * j + q) ^ ((lrow / RPB) & (CH - 1))) << 4) + g * 8) = pk.u;
+        }
+      wait_lds();
+#pragma unroll
+      for (int k = 0; k < 32 / RST; ++k) {
+        const int r = k * RST + lane / CH, ch = lane % CH;
+        const u32x4 val = *reinterpret_cast<const u32x4*>(slab + r * RS + ((ch ^ ((r / RPB) & (CH - 1))) << 4));
+        const int n = n0 + wn * C::WN + ch * 8;
+        const unsigned so = n < a.N ? (unsigned)(((wm * C::WM + i * 32 + r) * a.ldo + n) * 2) : 0x80000000u;
+        __builtin_amdgcn_raw_buffer_store_b128(val, os, so, 0, 0);
+      }
+      wait_lds();
+    }
   }
 }
 
@@ -724,6 +1027,27 @@ hipError_t launch_tile(const GemmArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int BM, int BN, int WGM, int WGN, int ST, int KS, int OUTF32>
+hipError_t launch_deep_t(const GemmArgs& a, hipStream_t s) {
+  using C = DCfg<BM, BN, WGM, WGN, ST, KS>;
+  static bool attr = false;   // raise the dynamic-LDS limit once per instantiation
+  if (!attr) {
+    const hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_deep_kernel<BM, BN, WGM, WGN, ST, KS, OUTF32>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+    if (e != hipSuccess) return e;
+    attr = true;
+  }
+  const long tiles = (long)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
+  hipLaunchKernelGGL((gemm_bf16_deep_kernel<BM, BN, WGM, WGN, ST, KS, OUTF32>), dim3((unsigned)tiles), dim3(C::NT), C::LDS, s,
+                     a);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WGM, int WGN, int ST, int KS>
+hipError_t launch_deep(const GemmArgs& a, hipStream_t s) {
+  return a.out_f32 ? launch_deep_t<BM, BN, WGM, WGN, ST, KS, 1>(a, s) : launch_deep_t<BM, BN, WGM, WGN, ST, KS, 0>(a, s);
+}
+
 template <int BM, int BN, int WGM, int WGN, int OUTF32, int RES = 0, int ROPE = 0>
 hipError_t launch_async_t(const GemmArgs& a, hipStream_t s) {
   using C = ACfg<BM, BN, WGM, WGN, OUTF32>;
@@ -839,6 +1163,68 @@ int device_cus() {
   return cus;
 }
 
+namespace {
+
+// The deep kernel's tiles, one workgroup per CU: a round of n tiles takes
+// k_tiles * step * (1 + slope * n / CUs) + epilogue us, the epilogue growing with
+// the share of the chip that writes at once (and with a residual, which is read).
+// Fitted to back-to-back launches of the encoders' shapes (M = 577 - 4,616, N =
+// 1,024 - 5,120, K = 1,024 - 5,120), which it reproduces within 6%.
+struct DeepOpt { const char* name; int bm, bn; double step, slope, e0, e1, r1; };
+constexpr DeepOpt kDeep[4] = {{"gemm_bf16_deep_64x64", 64, 64, 0.165, 0.20, 0.8, 1.2, 1.2},
+                              {"gemm_bf16_deep_64x128", 64, 128, 0.237, 0.34, 1.1, 0.8, 2.8},
+                              {"gemm_bf16_deep_128x128", 128, 128, 0.335, 0.35, 1.5, 2.0, 5.5},
+                              {"gemm_bf16_deep_192x128", 192, 128, 0.440, 0.33, 2.0, 3.2, 7.8}};
+constexpr double kDispatchUs = 2.5;   // a launch's own time between dependent kernels
+
+double deep_time(const DeepOpt& o, const GemmArgs& a, int cus) {
+  const long tiles = (long)((a.M + o.bm - 1) / o.bm) * ((a.N + o.bn - 1) / o.bn);
+  if (tiles > 2L * cus) return 1e300;   // beyond two rounds the persistent kernels win
+  double t = kDispatchUs;
+  for (long left = tiles; left > 0; left -= cus) {
+    const double load = (double)(left < cus ? left : cus) / cus;
+    t += a.K / BK * o.step * (1.0 + o.slope * load) + o.e0 + (a.resid ? o.r1 : o.e1) * load;
+  }
+  return t;
+}
+
+// The same for the kernel that would run otherwise: rounds of 256 x 256 or 256 x 128
+// tiles on a CU each, or of 128 x 128 tiles two to a CU.
+double plain_time(const GemmArgs& a, int cus) {
+  const int i = best_tile(a.M, a.N, nullptr, a.resid != nullptr);
+  const TileOpt& o = kTiles[i];
+  const long tiles = (long)((a.M + o.bm - 1) / o.bm) * ((a.N + o.bn - 1) / o.bn);
+  const long slots = i == 2 ? 2L * cus : cus;
+  const double area = i == 1 ? 0.62 : 1.0;   // of a 256 x 256 round
+  double t = kDispatchUs;
+  for (long left = tiles; left > 0; left -= slots) {
+    const double load = (double)(left < slots ? left : slots) / slots;
+    t += i == 2 ? a.K / BK * (0.35 + 0.60 * load) + 2.0 + (a.resid ? 8.0 : 4.0) * load
+                : area * (a.K / BK * (1.00 + 0.65 * load) + 2.0 + (a.resid ? 9.0 : 3.0) * load);
+  }
+  return t;
+}
+
+// Tile of the deep kernel when it is the fastest choice by 5% (the estimates'
+// error), else -1.  The residual
+// rows that a micro-batch half leaves after whole rounds of 256 x 256 tiles
+// (`beside`) stay on the persistent residual kernel: that launch runs beside the
+// other half's kernels, which need the CUs' LDS too (CLIP x64: 1%).
+int best_deep(const GemmArgs& a) {
+  if (!tile_rows_fit(a) || (uintptr_t)a.bias % 8 || (a.pos && !a.out_f32)) return -1;
+  if (a.beside && a.resid && async_res_ok(a)) return -1;
+  const int cus = device_cus();
+  int best = -1;
+  double best_t = 0.95 * plain_time(a, cus);
+  for (int i = 0; i < 4; ++i) {
+    const double t = deep_time(kDeep[i], a, cus);
+    if (t < best_t) { best_t = t; best = i; }
+  }
+  return best;
+}
+
+}  // namespace
+
 bool gemm_bf16_rope_ok(const GemmArgs& a) {
   return tile_ok(a) && !a.out_f32 && !a.resid && !a.pos && a.rope_hd > 0 && a.rope_hd % 8 == 0 && a.rope_hd <= 128 &&
          a.rope_hd_inv == rope_hd_inv(a.rope_hd) && a.rope_cols % a.rope_hd == 0 && a.rope_cols <= a.N && a.N < 65536;
@@ -849,31 +1235,15 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s, const char** kname
   if (!tile_ok(a)) return launch_gemm_bf16_staged(a, s, kname);
   // Pick the tile by estimated time.  All tiles sum k in the same order, so
   // the choice never changes a result.
-  // Launches that leave CUs idle even with 128 x 128 tiles are latency-bound:
-  // smaller tiles multiply the workgroups and three stages keep two k-tiles in
-  // flight -- 64 x 128 (4 waves of 32 x 64), or 64 x 64 (4 waves of 32 x 32)
-  // while 64 x 128 tiles would leave a quarter of the CUs idle.
-  // The residual rows a micro-batch half leaves after whole rounds of 256 x 256
-  // tiles stay on the persistent residual kernel even when they are few: that
-  // launch runs beside the other half's kernels, and measured 1% faster there
-  // end to end than the latency tiles (CLIP x64).  Alone on the chip (CLIP x4)
-  // the latency tiles are faster.
-  const int cus = device_cus();
-  const long t128 = (long)((a.M + 127) / 128) * ((a.N + 127) / 128);
-  if (t128 <= cus && !(a.beside && a.resid && async_res_ok(a))) {
-    // When every tile gets a CU of its own, deeper pipelines (6 stages of 64 x 64,
-    // 96 KB; 4 of 64 x 128, 96 KB) keep more k-tiles in flight: one CLIP image
-    // +4%, one Whisper clip +1%.  With more tiles than CUs the three-stage forms
-    // stay, as two of their workgroups fit in one CU's LDS (6 stages there: two
-    // images -17%).
-    if ((long)((a.M + 63) / 64) * ((a.N + 127) / 128) * 4 <= 3L * cus) {
-      *kname = "gemm_bf16_64x64";
-      if ((long)((a.M + 63) / 64) * ((a.N + 63) / 64) <= cus) return launch_tile<64, 64, 2, 2, 6>(a, s);
-      return launch_tile<64, 64, 2, 2, 3>(a, s);
+  const int deep = best_deep(a);
+  if (deep >= 0) {
+    *kname = kDeep[deep].name;
+    switch (deep) {
+      case 0: return a.K % (2 * BK) == 0 ? launch_deep<64, 64, 2, 2, 4, 2>(a, s) : launch_deep<64, 64, 2, 2, 6, 1>(a, s);
+      case 1: return launch_deep<64, 128, 2, 4, 6, 1>(a, s);
+      case 2: return launch_deep<128, 128, 4, 2, 4, 1>(a, s);
+      default: return launch_deep<192, 128, 2, 4, 4, 1>(a, s);
     }
-    *kname = "gemm_bf16_64x128";
-    if ((long)((a.M + 63) / 64) * ((a.N + 127) / 128) <= cus) return launch_tile<64, 128, 2, 2, 4>(a, s);
-    return launch_tile<64, 128, 2, 2, 3>(a, s);
   }
   const bool res = a.resid != nullptr;
   if (async_res_ok(a)) switch (best_tile(a.M, a.N, nullptr, true)) {
