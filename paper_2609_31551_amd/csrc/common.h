@@ -96,6 +96,7 @@ struct GemmArgs {
   void* out; int ldo; int out_f32;
   int beside;                      // the rows a half leaves after whole rounds of 256 x 256 tiles,
                                    // launched while the other half's kernels run on another stream
+  int shared;                      // any launch of a half: the other half's kernels want CUs meanwhile
   // Rotary positions applied in the epilogue of the bf16 q | k | v projection
   // (rope_pos set): output columns [0, rope_cols) are the q and k heads, rope_hd
   // columns each, in interleaved order -- column 2i of a head holds its x_i and

@@ -420,7 +420,8 @@ GemmArgs gemm_args(int M, int N, int K, const void* A, int lda, const void* B, i
 
 eas_status gemm_launch(eas_encoder* e, const GemmArgs& g, hipStream_t s);
 
-eas_status gemm(eas_encoder* e, const GemmArgs& g, hipStream_t s) {
+eas_status gemm(eas_encoder* e, GemmArgs g, hipStream_t s) {
+  g.shared = e->halves;
   if (e->cfg.dtype == EAS_BF16) {
     const int h = gemm_bf16_head_rows(g);
     if (h > 0) {

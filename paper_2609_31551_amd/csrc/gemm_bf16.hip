@@ -44,7 +44,16 @@ namespace {
 
 constexpr int BK = 64;
 constexpr int kResAhead = 1;
-constexpr int kStoreNT = 2;    // buffer-store cache policy: non-temporal (NT bit)
+// Buffer-store cache policies of the bf16 outputs.  Written through (SC1), an output
+// leaves as fast as a non-temporal one and is still in the last-level cache when the
+// next kernel reads it: FC1 + FC2 of five images 68.0 -> 60.0 us, of one 3,072-token
+// image 91.8 -> 79.7, with the weights in that cache too.  An output that would push
+// the rest out of the 256 MB cache goes non-temporal: over 84 MB (an 8,192-token
+// clip, 84 MB: written through 1.1% faster; 64 images in one pass, 302 MB: slower), or
+// over 64 MB for each of two halves side by side (16 images, 38 MB a half: 3.4%
+// faster; 24, 57 MB: 1.4% faster; 48, 85 MB: 0.6% slower; 64, 151 MB: 1.6% slower).
+constexpr int kStoreNT = 2, kStoreThrough = 16;
+constexpr long kThroughBytes = 84l << 20, kThroughBytesShared = 64l << 20;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 // M0 carries the LDS base of each DMA; nothing else in these kernels uses M0
@@ -572,7 +581,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_deep_kernel(GemmArgs
           }
           __builtin_amdgcn_raw_buffer_store_b128(
               (u32x4){__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])}, os,
-              st0 + (unsigned)(p * 8 * a.ldo * 4), 0, 0);
+              st0 + (unsigned)(p * 8 * a.ldo * 4), 0, kStoreThrough);
         }
         wait_lds();   // the reads are done before the next block overwrites the slab
       }
@@ -624,7 +633,7 @@ if (a.resid) {   // one launch a call (a CLS model's last layer with bf16 output
         const u32x4 val = *reinterpret_cast<const u32x4*>(slab + r * RS + ((ch ^ ((r / RPB) & (CH - 1))) << 4));
         const int n = n0 + wn * C::WN + ch * 8;
         const unsigned so = n < a.N ? (unsigned)(((wm * C::WM + i * 32 + r) * a.ldo + n) * 2) : 0x80000000u;
-        __builtin_amdgcn_raw_buffer_store_b128(val, os, so, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(val, os, so, 0, kStoreThrough);
       }
       wait_lds();
     }
@@ -662,7 +671,7 @@ struct ACfg : Cfg<BM, BN, WGM, WGN> {
   __device__ static int sw16(int row) { return (row >> 2) & 3; }   // 16-byte chunk swizzle of 64-byte rows
 };
 
-template <int BM, int BN, int WGM, int WGN, int OUTF32, int RES = 0, int ROPE = 0>
+template <int BM, int BN, int WGM, int WGN, int OUTF32, int RES, int ROPE, int THROUGH>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_async_kernel(GemmArgs a, int n_tiles) {
   using C = ACfg<BM, BN, WGM, WGN, OUTF32>;
   constexpr int S = C::FM * C::FN * 2 * (OUTF32 ? 2 : 1);   // buffer stores per wave per tile
@@ -928,11 +937,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_async_kernel(GemmArg
         for (int k = 0; k < 32 / RST; ++k) {
           const u32x4 val = *reinterpret_cast<const u32x4*>(stg + (((k * RST) & 7) ? rd1 : rd0) + k * RST * RS);
           // rows past M fall outside the buffer's range; columns past N were sent out of range
-          // non-temporal: the output is not re-read by this kernel, and
-          // keeping it out of the L2's working set leaves the operand
-          // panels there (+2.5% kernel rate on CLIP's QKV / FC1)
           __builtin_amdgcn_raw_buffer_store_b128(val, out_rsrc, st0 + (unsigned)((i * 32 + k * RST) * a.ldo * 2), 0,
-                                                 kStoreNT);
+                                                 THROUGH ? kStoreThrough : kStoreNT);
         }
         wait_lds();   // the reads are done before the next block row overwrites the staging
       }
@@ -1048,10 +1054,10 @@ hipError_t launch_deep(const GemmArgs& a, hipStream_t s) {
   return a.out_f32 ? launch_deep_t<BM, BN, WGM, WGN, ST, KS, 1>(a, s) : launch_deep_t<BM, BN, WGM, WGN, ST, KS, 0>(a, s);
 }
 
-template <int BM, int BN, int WGM, int WGN, int OUTF32, int RES = 0, int ROPE = 0>
-hipError_t launch_async_t(const GemmArgs& a, hipStream_t s) {
+template <int BM, int BN, int WGM, int WGN, int OUTF32, int RES, int ROPE, int THROUGH>
+hipError_t launch_async_k(const GemmArgs& a, hipStream_t s) {
   using C = ACfg<BM, BN, WGM, WGN, OUTF32>;
-  auto kern = gemm_bf16_async_kernel<BM, BN, WGM, WGN, OUTF32, RES, ROPE>;
+  auto kern = gemm_bf16_async_kernel<BM, BN, WGM, WGN, OUTF32, RES, ROPE, THROUGH>;
   static int slots = 0;   // co-resident workgroups on this device, found once per instantiation
   if (!slots) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
@@ -1069,6 +1075,13 @@ hipError_t launch_async_t(const GemmArgs& a, hipStream_t s) {
   const int grid = (int)(tiles < slots ? tiles : slots);
   hipLaunchKernelGGL(kern, dim3(grid), dim3(C::NT), C::LDS, s, a, (int)tiles);
   return hipGetLastError();
+}
+
+template <int BM, int BN, int WGM, int WGN, int OUTF32, int RES = 0, int ROPE = 0>
+hipError_t launch_async_t(const GemmArgs& a, hipStream_t s) {
+  if constexpr (!OUTF32)
+    if ((long)a.M * a.N * 2 <= (a.shared ? kThroughBytesShared : kThroughBytes)) return launch_async_k<BM, BN, WGM, WGN, OUTF32, RES, ROPE, 1>(a, s);
+  return launch_async_k<BM, BN, WGM, WGN, OUTF32, RES, ROPE, 0>(a, s);
 }
 
 template <int BM, int BN, int WGM, int WGN>
@@ -1179,7 +1192,12 @@ constexpr double kDispatchUs = 2.5;   // a launch's own time between dependent k
 
 double deep_time(const DeepOpt& o, const GemmArgs& a, int cus) {
   const long tiles = (long)((a.M + o.bm - 1) / o.bm) * ((a.N + o.bn - 1) / o.bn);
-  if (tiles > 2L * cus) return 1e300;   // beyond two rounds the persistent kernels win
+  // beyond two rounds the persistent kernels win; beside another half's kernels,
+  // which a second round of whole CUs would hold up, beyond one (32 images: 5%)
+  if (tiles > (a.shared ? 1L : 2L) * cus) return 1e300;
+  // such a half's tail leaves the other half a quarter of the CUs (24 images, a tail
+  // of 216 tiles: 1.5% slower; 16 images, 160 tiles: 1.8% faster)
+  if (a.beside && 4 * tiles > 3L * cus) return 1e300;
   double t = kDispatchUs;
   for (long left = tiles; left > 0; left -= cus) {
     const double load = (double)(left < cus ? left : cus) / cus;
@@ -1239,7 +1257,7 @@ hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s, const char** kname
   if (deep >= 0) {
     *kname = kDeep[deep].name;
     switch (deep) {
-      case 0: return a.K % (2 * BK) == 0 ? launch_deep<64, 64, 2, 2, 4, 2>(a, s) : launch_deep<64, 64, 2, 2, 6, 1>(a, s);
+      case 0: return a.K % (2 * BK) == 0 ? launch_deep<64, 64, 2, 2, 5, 2>(a, s) : launch_deep<64, 64, 2, 2, 6, 1>(a, s);
       case 1: return launch_deep<64, 128, 2, 4, 6, 1>(a, s);
       case 2: return launch_deep<128, 128, 4, 2, 4, 1>(a, s);
       default: return launch_deep<192, 128, 2, 4, 4, 1>(a, s);
