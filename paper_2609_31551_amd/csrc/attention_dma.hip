@@ -86,14 +86,33 @@ __device__ __forceinline__ void decode(const AttnWork& w, int tile, int qt, int*
   *q0 = *s0 + (tile - w.tile_start[i]) * qt;
 }
 
+// One dword of every 128-byte line of this block's share of [a.ahead, a.ahead +
+// a.ahead_bytes): AHEAD_LINES lines a thread, block b's after block b - 1's.
+constexpr int AHEAD_LINES = 4;
+template <int NT>
+__device__ __forceinline__ void read_ahead(const AttnArgs& a, int b) {
+  unsigned v[AHEAD_LINES];
+#pragma unroll
+  for (int u = 0; u < AHEAD_LINES; ++u) {
+    const long o = (((long)b * AHEAD_LINES + u) * NT + threadIdx.x) * 128;
+    v[u] = *reinterpret_cast<const unsigned*>(a.ahead + (o < a.ahead_bytes ? o : a.ahead_bytes - 4));
+  }
+#pragma unroll
+  for (int u = 0; u < AHEAD_LINES; ++u) asm volatile("" ::"v"(v[u]));   // the values themselves are not needed
+}
+
 // Held to 128 VGPRs (4 waves per SIMD) explicitly: left to itself the register
 // allocator takes 130 (head_dim 80, and 64 with the staged output) and loses a
 // wave per SIMD
 template <int HD, int QB, int QT>
 __global__ __launch_bounds__(QT / QB * 2)
 __attribute__((amdgpu_waves_per_eu(4, HD > 64 ? 4 : 8)))
-void attn_bf16_dma_kernel(AttnArgs a, AttnWork w) {
+void attn_bf16_dma_kernel(AttnArgs a, AttnWork w, int work_blocks) {
   using C = AttnCfg<HD, QB, QT>;
+  if ((int)blockIdx.x >= work_blocks) {
+    read_ahead<64 * C::NW>(a, blockIdx.x - work_blocks);
+    return;
+  }
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) char*)smem);
   const int h = blockIdx.x % a.heads;
@@ -384,8 +403,11 @@ template <int HD, int QB, int QT>
 hipError_t launch_hd(const AttnArgs& a, const AttnWork& w, int total_tiles, hipStream_t s) {
   using C = AttnCfg<HD, QB, QT>;
   constexpr int lds = 2 * C::BUF;
-  hipLaunchKernelGGL((attn_bf16_dma_kernel<HD, QB, QT>), dim3((unsigned)(total_tiles * a.heads)), dim3(64 * C::NW), lds,
-                     s, a, w);
+  const int work_blocks = total_tiles * a.heads;
+  constexpr long per = 64L * C::NW * 128 * AHEAD_LINES;
+  const int ahead_blocks = a.ahead ? (int)((a.ahead_bytes + per - 1) / per) : 0;
+  hipLaunchKernelGGL((attn_bf16_dma_kernel<HD, QB, QT>), dim3((unsigned)(work_blocks + ahead_blocks)),
+                     dim3(64 * C::NW), lds, s, a, w, work_blocks);
   return hipGetLastError();
 }
 

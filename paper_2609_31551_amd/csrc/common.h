@@ -166,6 +166,9 @@ struct AttnArgs {
   void* out; int ldo;              // [N, ldo]
   int heads, hd;
   float scale;                     // 1 / sqrt(hd)
+  // Weights of the launches that follow, [ahead, ahead + ahead_bytes), which the
+  // DMA kernel's extra blocks pull into the last-level cache, or null
+  const char* ahead; long ahead_bytes;
 };
 hipError_t launch_attention_bf16(const AttnArgs& a, const AttnWork& w, int total_tiles, int N, hipStream_t s,
                                  const char** kname);
