@@ -146,6 +146,7 @@ __device__ __forceinline__ void rope_rotate(float& x, float& y, float turns) {
 
 // ---- launchers (each returns hipGetLastError() of its launch) --------------
 hipError_t launch_gemm_bf16(const GemmArgs& a, hipStream_t s, const char** kname);
+int device_cus();   // compute units of the current device
 inline unsigned rope_hd_inv(int hd) { return (unsigned)((0x100000000ull + (unsigned)hd - 1) / (unsigned)hd); }
 // Whether launch_gemm_bf16 runs these arguments with the rotary epilogue (the
 // DMA kernels' operand and epilogue requirements, bf16 output, head_dim % 8 == 0).
