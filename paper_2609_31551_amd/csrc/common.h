@@ -77,6 +77,58 @@ __device__ __forceinline__ int find_seq(const int* cu, int n, int r) {
   return lo;
 }
 
+__device__ __forceinline__ float wave_sum(float v) {
+  // Butterfly: v += v[lane ^ o] for o = 32, 16, 8, 4, 2, 1, each lane move in
+  // VALU (no LDS round trip): the two swaps pair lanes 32 and 16 apart, a
+  // rotation by 8 within each 16-lane row gives lane ^ 8, shifts by 4 (the one
+  // whose source stays in the row) lane ^ 4, quad permutations lane ^ 2 and
+  // lane ^ 1.  Every lane ends with the same sum, summed in a fixed order.
+  {
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+  {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+  }
+  const int lane = __lane_id();
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, false));   // row_ror:8
+  {
+    const int up = __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x104, 0xF, 0xF, false);   // row_shl:4 (lane + 4)
+    const int dn = __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x114, 0xF, 0xF, false);   // row_shr:4 (lane - 4)
+    v += __int_as_float((lane & 4) ? dn : up);
+  }
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));  // quad_perm 2,3,0,1
+  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));  // quad_perm 1,0,3,2
+  return v;
+}
+
+constexpr int LN_MAXE = 32;   // elements per lane: rows up to 64 * 32 = 2048 wide
+
+// One wave per row: mean, then the population variance of (x - mean).  The
+// reduction order is fixed, so a row's statistics depend only on that row.
+__device__ __forceinline__ void row_stats(const float* xr, int d, float eps, float* v, float* mu, float* rstd) {
+  const int lane = threadIdx.x & 63;
+  float s = 0.0f;
+#pragma unroll
+  for (int e = 0; e < LN_MAXE; ++e) {
+    const int c = lane + 64 * e;
+    v[e] = c < d ? xr[c] : 0.0f;
+    s += v[e];
+  }
+  const float mean = wave_sum(s) / (float)d;
+  float q = 0.0f;
+#pragma unroll
+  for (int e = 0; e < LN_MAXE; ++e) {
+    const int c = lane + 64 * e;
+    const float t = c < d ? v[e] - mean : 0.0f;
+    q += t * t;
+  }
+  const float var = wave_sum(q) / (float)d;
+  *mu = mean;
+  *rstd = 1.0f / sqrtf(var + eps);
+}
+
 // Fused GEMM epilogue / prologue description:
 //   out[m, n] = act(sum_k A'[m, k] * B[n, k] + bias[n]) + pos[idx(m), n] + resid[m, n]
 // where A' is A itself, or LayerNorm(A) when `stats` is set:
@@ -88,6 +140,7 @@ struct GemmArgs {
   const void* B; int ldb;          // [N, ldb] model dtype
   const float2* stats;             // per token (mean, rstd) or null
   const void* ln_g; const void* ln_b; int ln_dim; int ln_group;
+  float ln_eps;                    // fp32 mode, ln_g set without stats: the GEMM computes them itself
   const void* bias;                // [N] model dtype or null
   int act;
   const void* pos; int pos_f32; int ld_pos;   // position table (model dtype or fp32)
@@ -161,6 +214,9 @@ int gemm_bf16_head_rows(const GemmArgs& a);
 GemmArgs gemm_rows(const GemmArgs& a, int m0, int m1);
 hipError_t launch_gemm_bf16_staged(const GemmArgs& a, hipStream_t s, const char** kname);
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t s, const char** kname);
+// Whether launch_gemm_f32 takes the LayerNorm statistics of these arguments (ln_g set)
+// into its own launch; otherwise they are passed in `stats`.
+bool gemm_f32_own_stats(const GemmArgs& a);
 
 struct AttnArgs {
   const void* qkv; int ldqkv;      // [N, ldqkv]: q | k | v blocks of width heads*hd

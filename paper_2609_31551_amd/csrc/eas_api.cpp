@@ -452,13 +452,15 @@ eas_status ln_gemm(eas_encoder* e, const Workspace& w, GemmArgs g, float eps, in
   const int dim = g.ln_dim, rows = g.M * group;
   const float* x = static_cast<const float*>(g.A);
   if (e->cfg.dtype != EAS_BF16) {
+    g.ln_group = group;
+    g.ln_eps = eps;
+    if (gemm_f32_own_stats(g)) return gemm(e, g, s);
     eas_status rc = run(e, s, 0.0, (double)rows * (dim * 4 + 8), [&](const char** kn) {
       *kn = "ln_stats";
       return launch_ln_stats(x, rows, dim, eps, w.stats, s);
     });
     if (rc != EAS_OK) return rc;
     g.stats = w.stats;
-    g.ln_group = group;
     return gemm(e, g, s);
   }
   eas_status rc = run(e, s, 0.0, (double)rows * dim * 6, [&](const char** kn) {

@@ -38,58 +38,6 @@ __global__ void positions_kernel(SeqMeta m, int N, int4* pos3, int* tab_idx, int
   tab_idx[i] = m.cls + p.y * pos_gw + p.z;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-  // Butterfly: v += v[lane ^ o] for o = 32, 16, 8, 4, 2, 1, each lane move in
-  // VALU (no LDS round trip): the two swaps pair lanes 32 and 16 apart, a
-  // rotation by 8 within each 16-lane row gives lane ^ 8, shifts by 4 (the one
-  // whose source stays in the row) lane ^ 4, quad permutations lane ^ 2 and
-  // lane ^ 1.  Every lane ends with the same sum, summed in a fixed order.
-  {
-    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-  }
-  {
-    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-  }
-  const int lane = __lane_id();
-  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, false));   // row_ror:8
-  {
-    const int up = __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x104, 0xF, 0xF, false);   // row_shl:4 (lane + 4)
-    const int dn = __builtin_amdgcn_mov_dpp(__float_as_int(v), 0x114, 0xF, 0xF, false);   // row_shr:4 (lane - 4)
-    v += __int_as_float((lane & 4) ? dn : up);
-  }
-  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, false));  // quad_perm 2,3,0,1
-  v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));  // quad_perm 1,0,3,2
-  return v;
-}
-
-constexpr int LN_MAXE = 32;   // elements per lane: rows up to 64 * 32 = 2048 wide
-
-// One wave per row: mean, then the population variance of (x - mean).  The
-// reduction order is fixed, so a row's statistics depend only on that row.
-__device__ __forceinline__ void row_stats(const float* xr, int d, float eps, float* v, float* mu, float* rstd) {
-  const int lane = threadIdx.x & 63;
-  float s = 0.0f;
-#pragma unroll
-  for (int e = 0; e < LN_MAXE; ++e) {
-    const int c = lane + 64 * e;
-    v[e] = c < d ? xr[c] : 0.0f;
-    s += v[e];
-  }
-  const float mean = wave_sum(s) / (float)d;
-  float q = 0.0f;
-#pragma unroll
-  for (int e = 0; e < LN_MAXE; ++e) {
-    const int c = lane + 64 * e;
-    const float t = c < d ? v[e] - mean : 0.0f;
-    q += t * t;
-  }
-  const float var = wave_sum(q) / (float)d;
-  *mu = mean;
-  *rstd = 1.0f / sqrtf(var + eps);
-}
-
 __global__ __launch_bounds__(256) void ln_stats_kernel(const float* x, int N, int d, float eps, float2* st) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (row >= N) return;
