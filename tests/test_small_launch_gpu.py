@@ -1,0 +1,69 @@
+"""Kernels that only small launches take, at their tile edges: the
+deep-pipelined bf16 GEMM (64 x 64 to 192 x 128 tiles, steps of 64 or 128 k) and
+the fp32 GEMM's 16 x 16 tiles with their own LayerNorm statistics.  Every kernel
+sums k in the same order, so a request alone must equal the same request inside a
+micro-batch that takes the persistent kernels (or the 64 x 64 fp32 tiles) bit
+for bit; the request alone is also checked against the float64 reference."""
+import numpy as np
+import pytest
+
+from _harness import TOL, gpu_encode, oracle_encode, rel_err
+from paper_2609_31551_amd import configs as C
+from paper_2609_31551_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# (patch rows, patch columns): 4 to 580 tokens, one merge window around the edges
+# of 64, 128 and 192 rows, and one and two tiles per CU of the column counts
+GRIDS = [(2, 2), (2, 30), (8, 8), (2, 34), (2, 62), (8, 16), (2, 66), (2, 94), (12, 16), (14, 14), (2, 290)]
+
+
+def _alone_and_batched(p, grids, rest):
+    W = synth.make_weights(p, 0)
+    tp, patch = p["temporal_patch"], p["patch"]
+    shapes = [(tp, patch * h, patch * w) for h, w in grids + rest]
+    items = synth.make_items(p, len(shapes), 0, shapes=shapes)
+    batch = gpu_encode(p, items, W)
+    cu = batch["cu_out"]
+    for r, (h, w) in enumerate(grids):
+        print("[small] %s: %d tokens alone" % (p["name"], h * w), flush=True)
+        alone = gpu_encode(p, [items[r]], W)
+        np.testing.assert_array_equal(alone["out"], batch["out"][cu[r]:cu[r + 1]])
+        e = rel_err(alone["out"], oracle_encode(p, [items[r]], W)["out"])
+        assert e <= TOL[p["dtype"]], (h, w, e)
+
+
+def test_deep_gemm_tile_edges():
+    """1280 / 5120 / 3584 columns, k of 1216 (steps of 64), 1280 and 5120 (of 128);
+    the batch of 9,000 more tokens runs as two halves on the persistent kernels."""
+    _alone_and_batched(C.with_layers(C.QWEN_IMAGE, 1), GRIDS, [(48, 48)] * 4)
+
+
+def test_deep_gemm_odd_widths():
+    """A hidden width that ends inside every column tile (320 = 2 x 128 + 64, k of five
+    64-steps: no 128-steps) and a 160-wide output."""
+    p = dict(C.with_layers(C.QWEN_IMAGE, 2), name="qwen_w320", hidden=320, heads=4, mlp=448, out_dim=160)
+    _alone_and_batched(p, GRIDS, [(48, 48)] * 4)
+
+
+def test_cls_model_bf16_output_small():
+    """The last FC2 of a CLS model with bf16 output adds its residual in the deep
+    kernel's bf16 epilogue: it must equal the fp32 output rounded once."""
+    import torch
+    p = C.with_layers(C.CLIP_L336, 1)
+    W = synth.make_weights(p, 0)
+    items = synth.make_items(p, 1, 0)
+    f32 = gpu_encode(p, items, W)["out"]
+    b16 = gpu_encode(p, items, W, out_dtype="bf16")["out"]
+    want = torch.from_numpy(np.asarray(f32, np.float32)).bfloat16().float().numpy()
+    np.testing.assert_array_equal(np.asarray(b16, np.float32), want)
+
+
+@pytest.mark.parametrize("width", [320, 96])
+def test_fp32_small_tiles(width):
+    """16 x 16 fp32 tiles with their own LayerNorm statistics against the 64 x 64
+    tiles and the statistics kernel, which the batch of 2,304 more tokens takes
+    for at least the wide products."""
+    p = dict(C.with_layers(C.QWEN_IMAGE, 1), name="qwen_f32_w%d" % width, dtype="fp32", hidden=width,
+             heads=width // 16, head_dim=16, mlp=1280, out_dim=40, rope_sections=(0, 4, 4))
+    _alone_and_batched(p, [(2, 2), (2, 6), (4, 4), (2, 10), (8, 8), (2, 34)], [(48, 48)])
