@@ -122,8 +122,10 @@ TRAFFIC_SOURCES = {
     "gemm_bf16_async_res_128x128": ("gemm_bf16.hip", "common.h", "eas_api.cpp"),
     "gemm_bf16_async_256x128": ("gemm_bf16.hip", "common.h", "eas_api.cpp"),
     "gemm_bf16_async_128x128": ("gemm_bf16.hip", "common.h", "eas_api.cpp"),
-    "gemm_bf16_64x64": ("gemm_bf16.hip", "common.h", "eas_api.cpp"),
-    "gemm_bf16_64x128": ("gemm_bf16.hip", "common.h", "eas_api.cpp"),
+    "gemm_bf16_deep_64x64": ("gemm_bf16.hip", "common.h", "eas_api.cpp"),
+    "gemm_bf16_deep_64x128": ("gemm_bf16.hip", "common.h", "eas_api.cpp"),
+    "gemm_bf16_deep_128x128": ("gemm_bf16.hip", "common.h", "eas_api.cpp"),
+    "gemm_bf16_deep_192x128": ("gemm_bf16.hip", "common.h", "eas_api.cpp"),
     "attn_bf16_hd64": ("attention_dma.hip", "common.h", "eas_api.cpp"),
     "attn_bf16_hd80": ("attention_dma.hip", "common.h", "eas_api.cpp"),
     "attn_bf16_hd80_q256": ("attention_dma.hip", "common.h", "eas_api.cpp"),
