@@ -257,46 +257,63 @@ __global__ void pack_vision_kernel(PackArgs p, int cls, int merge, int patch, in
   out[idx] = (T)p.src[r][src];
 }
 
-// bf16 packer: a block packs `tpb` consecutive token rows.  One thread per
-// (token, c, tau, dy) line of `patch` pixels reads them as float2 pairs and
-// writes the bf16 values into the block's LDS copy of the rows; the block then
-// stores the rows' contiguous span with 8-byte writes, so every output line is
-// written whole (patch even, every image width even, 8-byte aligned sources,
-// lines <= 256, patch <= 16).
+// bf16 packer: a block packs a strip of up to STRIP patches side by side (with the
+// merger, the two patch rows of its windows), whose token rows are consecutive in
+// storage order.  Consecutive threads read consecutive float2 pairs of an image row
+// (224 bytes a strip) and write them as bf16 into the block's LDS copy of the token
+// rows, which then leaves as one contiguous span of 8-byte writes.  Bound by memory;
+// with a thread per 14-pixel line instead, a wave's loads touched 64 lines each
+// (16 frames of 448 x 448: 45 -> 20 us, 2.9 TB/s; one 672 x 896 image 16 -> 12 us;
+// one 336 x 336 image 5.2 -> 5.6 us, its call unchanged).  Needs an even patch, even widths and 8-byte aligned sources.
+constexpr int STRIP = 4;
 __global__ __launch_bounds__(256) void pack_vision_vec_kernel(PackArgs p, int cls, int merge, int patch, int tp, int K,
-                                                              int lines, int tpb, int rows, bf16* out) {
-  __shared__ __attribute__((aligned(16))) unsigned buf[256 * 16 / 2];   // tpb * K bf16
-  const int row0 = blockIdx.x * tpb, nrows = min(tpb, rows - row0);
-  const int t = threadIdx.x / lines, ln = threadIdx.x % lines;
-  if (t < nrows) {
-    const int row = row0 + t;
-    unsigned* dst = buf + (t * K + ln * patch) / 2;
-    const int r = find_seq(p.cu, p.n, row);
-    int j = row - p.cu[r];
-    if (cls && j == 0) {
-      for (int x = 0; x < patch / 2; ++x) dst[x] = 0u;
-    } else {
-      j -= cls;
-      const int dy = ln % patch, tau = (ln / patch) % tp, c = ln / (patch * tp);
-      const int H = p.tchw[r][2], W = p.tchw[r][3], C = p.tchw[r][1];
-      int ti, hi, wi;
-      decode_token(j, H / patch, W / patch, merge, &ti, &hi, &wi);
-      const float2* src = reinterpret_cast<const float2*>(
-          p.src[r] + (((long)(ti * tp + tau) * C + c) * H + hi * patch + dy) * W + wi * patch);
-      for (int x = 0; x < patch / 2; ++x) {
-        const float2 v = src[x];
+                                                              bf16* out) {
+  extern __shared__ __attribute__((aligned(16))) unsigned buf[];   // STRIP * merge token rows of K bf16
+  const int r = find_seq(p.strip0, p.n, blockIdx.x);
+  const int H = p.tchw[r][2], W = p.tchw[r][3], C = p.tchw[r][1], h = H / patch, w = W / patch;
+  const int per_row = (w + STRIP - 1) / STRIP, rows_n = h / merge;   // strips a patch row, patch rows (pairs) a grid
+  const int q = blockIdx.x - p.strip0[r], ti = q / (per_row * rows_n), rq = q % (per_row * rows_n);
+  const int hi = rq / per_row * merge, wi = rq % per_row * STRIP, wp = min(STRIP, w - wi);
+  // 32 threads an image row of the strip (at most 4 * 8 float2 pairs), 8 rows at a time
+  const int hp = patch / 2, tx = threadIdx.x & 31, px = tx / hp, dx = tx - px * hp;
+  const bool on = px < wp;
+  const int rows = merge * patch, nr = C * tp * rows;
+  const int row2 = K / 2;                               // 4-byte words a token row
+  const int tokx = merge == 2 ? (px >> 1) * 4 + (px & 1) : px;
+  const float* base = p.src[r] + ((long)ti * tp * C * H + (long)hi * patch) * W + (long)wi * patch + (on ? 2 * tx : 0);
+  constexpr int U = 4;
+  for (int e0 = threadIdx.x >> 5; e0 < nr; e0 += U * 8) {
+    float2 v[U];
+    int dst[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int er = min(e0 + u * 8, nr - 1);           // past the end: the last row again
+      const int pl = er / rows, y = er - pl * rows, tau = pl / C, c = pl - tau * C;
+      const int py = y >= patch ? 1 : 0;
+      v[u] = *reinterpret_cast<const float2*>(base + ((long)pl * H + y) * W);
+      dst[u] = (tokx + 2 * py) * row2 + ((c * tp + tau) * patch + y - py * patch) * hp + dx;
+    }
+    if (on) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
         union { unsigned u; bf16 h[2]; } o;
-        o.h[0] = (bf16)v.x;
-        o.h[1] = (bf16)v.y;
-        dst[x] = o.u;
+        o.h[0] = (bf16)v[u].x;
+        o.h[1] = (bf16)v[u].y;
+        buf[dst[u]] = o.u;
       }
     }
   }
   __syncthreads();
-  const int n8 = nrows * K / 4;   // 8-byte pieces of the block's rows (K % 4 == 0)
-  uint2* o8 = reinterpret_cast<uint2*>(out + (long)row0 * K);
+  // first token of the strip: whole patch rows (or pairs) before it, then merge * wi tokens
+  const long tok0 = p.cu[r] + cls + ((long)ti * h + hi) * w + (long)merge * wi;
+  const int n8 = merge * wp * K / 4;   // 8-byte pieces (K % 4 == 0)
+  uint2* o8 = reinterpret_cast<uint2*>(out + tok0 * K);
   const uint2* b8 = reinterpret_cast<const uint2*>(buf);
   for (int i = threadIdx.x; i < n8; i += blockDim.x) o8[i] = b8[i];
+  if (cls && q == 0) {   // the request's CLS row
+    uint2* c8 = reinterpret_cast<uint2*>(out + (long)p.cu[r] * K);
+    for (int i = threadIdx.x; i < K / 4; i += blockDim.x) c8[i] = make_uint2(0u, 0u);
+  }
 }
 
 // bf16 im2col for C % 8 == 0: one thread per (output frame, 8 channels) reads
@@ -514,13 +531,18 @@ hipError_t launch_im2col_k3(const void* src, int frames_in, int C, int n_clips, 
 hipError_t launch_pack_vision(const PackArgs& p, int cls, int merge, int patch, int tp, int K, int is_bf16,
                               void* packed, long total, hipStream_t s) {
   if (total == 0) return hipSuccess;
-  const int lines = K / patch;
-  bool vec = is_bf16 && patch % 2 == 0 && patch <= 16 && lines <= 256 && (uintptr_t)packed % 8 == 0;
+  // with the merger every grid is even, so a strip holds whole windows
+  bool vec = is_bf16 && patch % 2 == 0 && patch <= 16 && K / patch <= 256 && (uintptr_t)packed % 8 == 0 && merge <= 2;
   for (int r = 0; vec && r < p.n; ++r) vec = p.tchw[r][3] % 2 == 0 && (uintptr_t)p.src[r] % 8 == 0;
   if (vec) {
-    const int rows = (int)(total / K), tpb = 256 / lines;
-    hipLaunchKernelGGL(pack_vision_vec_kernel, dim3((rows + tpb - 1) / tpb), dim3(256), 0, s, p, cls, merge, patch, tp,
-                       K, lines, tpb, rows, (bf16*)packed);
+    PackArgs q = p;
+    q.strip0[0] = 0;
+    for (int r = 0; r < p.n; ++r) {
+      const int t = p.tchw[r][0] / tp, h = p.tchw[r][2] / patch, w = p.tchw[r][3] / patch;
+      q.strip0[r + 1] = q.strip0[r] + t * (h / merge) * ((w + STRIP - 1) / STRIP);
+    }
+    hipLaunchKernelGGL(pack_vision_vec_kernel, dim3((unsigned)q.strip0[p.n]), dim3(256), (size_t)STRIP * merge * K * 2,
+                       s, q, cls, merge, patch, tp, K, (bf16*)packed);
     return hipGetLastError();
   }
   if (is_bf16)

@@ -67,3 +67,20 @@ def test_fp32_small_tiles(width):
     p = dict(C.with_layers(C.QWEN_IMAGE, 1), name="qwen_f32_w%d" % width, dtype="fp32", hidden=width,
              heads=width // 16, head_dim=16, mlp=1280, out_dim=40, rope_sections=(0, 4, 4))
     _alone_and_batched(p, [(2, 2), (2, 6), (4, 4), (2, 10), (8, 8), (2, 34)], [(48, 48)])
+
+
+@pytest.mark.parametrize("merge,tp", [(1, 2), (2, 2), (1, 1)])
+def test_pack_strips(merge, tp):
+    """The bf16 packer's strips of four patches: widths that end inside a strip, one
+    patch (or window) wide, several frames; exact against the reference's packing."""
+    from oracle import encoder as O
+    d = 320
+    p = dict(C.with_layers(C.QWEN_VIDEO, 1), name="pack_m%d_t%d" % (merge, tp), hidden=d, heads=4, mlp=448, merge=merge,
+             temporal_patch=tp, out_dim=160 if merge == 2 else d)
+    grids = [(1, 1), (1, 3), (3, 5), (2, 4), (5, 7)]
+    shapes = [(tp * (1 + r % 3), 14 * merge * h, 14 * merge * w) for r, (h, w) in enumerate(grids)]
+    items = synth.make_items(p, len(shapes), 0, shapes=shapes)
+    got = gpu_encode(p, items, synth.make_weights(p, 0))
+    want, cu, _ = O.pack(p, items)
+    np.testing.assert_array_equal(got["cu"], cu)
+    np.testing.assert_array_equal(got["packed"].reshape(-1), np.asarray(want, np.float32).reshape(-1))
