@@ -690,8 +690,8 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
     g1.bias = W(p + "fc1.b");
     g1.act = act;
     EAS_TRY(ln_gemm(enc, ws, g1, c.ln_eps, 1, s));
-    // the CLS model's output is the final residual stream: the last FC2 writes it directly
-    const bool direct = c.kind == EAS_KIND_VIT_CLS_ABS && l == c.layers - 1;
+    // without a connector the output is the final residual stream: the last FC2 writes it directly
+    const bool direct = vit && c.merge == 1 && l == c.layers - 1;
     GemmArgs g2 = gemm_args(N, d, f, ws.hbuf, f, W(p + "fc2.w"), f, direct ? out_embeddings : (void*)ws.x, d,
                             direct ? out_f32 : 1);
     g2.bias = W(p + "fc2.b");
@@ -718,7 +718,7 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
       *kn = "ln_apply";
       return launch_ln_apply(ws.x, N, d, c.ln_eps, W("ln_post.g"), W("ln_post.b"), bf, out_embeddings, out_f32, s);
     }));
-  } else if (c.layers == 0) {   // CLS model without layers: the embedding is the output
+  } else if (c.layers == 0) {   // no layers and no connector: the embedding is the output
     if (hipMemcpyAsync(out_embeddings, ws.x, (size_t)N * d * 4, hipMemcpyDeviceToDevice, s) != hipSuccess)
       return fail(enc, EAS_ERR_HIP, "hipMemcpyAsync failed");
   }
@@ -768,8 +768,8 @@ int split_point(const eas_encoder* e, const int32_t* cu, int n, int64_t* in_off,
 eas_status encode_call(eas_encoder* enc, const void* packed_in, const int32_t* cu_seqlens, const int32_t* grid_thw,
                        int32_t n_seqs, const void* weights, void* out_embeddings, int32_t* cu_out, hipStream_t s) {
   const eas_config& c = enc->cfg;
-  if (c.kind == EAS_KIND_VIT_CLS_ABS && c.layers == 0 && c.out_dtype != EAS_FP32)
-    return fail(enc, EAS_ERR_UNSUPPORTED, "zero-layer CLS model needs fp32 output");
+  if (c.kind != EAS_KIND_WHISPER && c.merge == 1 && c.layers == 0 && c.out_dtype != EAS_FP32)
+    return fail(enc, EAS_ERR_UNSUPPORTED, "a zero-layer encoder without a connector needs fp32 output");
   eas_status rc = EAS_OK;
   if (enc->kpad) {   // the zero-padded patch weight, shared by both halves of a split call
     const int K = (int)k_patch(c), kp = enc->kpad, d = c.hidden;

@@ -9,6 +9,9 @@ library must refuse.
   than max_tokens and a cu_seqlens / grid_thw mismatch are rejected on the host
   (the documented status, nothing written to the output), and the handle then
   encodes a valid micro-batch exactly as before.
+* Encoders without a connector (merge == 1) other than the CLS model: the final
+  residual stream is the output, in both output types; without layers the
+  embedding is, and only fp32 output is accepted.
 """
 import numpy as np
 import pytest
@@ -70,6 +73,30 @@ def test_refused_calls_write_nothing_and_leave_the_handle_usable():
     torch.cuda.synchronize()
     np.testing.assert_array_equal(again_cu, ref_cu)
     np.testing.assert_array_equal(again.cpu().numpy(), ref.numpy())
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("kind", [C.KIND_VIT_ROPE, C.KIND_VIT_ABS])
+def test_encoders_without_a_connector_write_the_residual_stream(kind, dtype):
+    import torch
+    from paper_2609_31551_amd import eas
+    for layers in (2, 0):
+        p = dict(C.with_layers(C.QWEN_IMAGE, layers), name="no_connector_%s_%s" % (kind, dtype), kind=kind, dtype=dtype,
+                 hidden=320, heads=4, mlp=448, merge=1, out_dim=320)
+        if kind == C.KIND_VIT_ABS:
+            p.update(rope_sections=(0, 0, 0), pos_grid=(6, 9))
+        W = synth.make_weights(p, 0)
+        items = synth.make_items(p, 3, 0, shapes=[(2, 70, 126), (2, 14, 14), (2, 84, 42)])
+        print("[edge] %s, %d layers" % (p["name"], layers), flush=True)
+        got = gpu_encode(p, items, W)
+        check_parity(p, got, oracle_encode(p, items, W))
+        if layers:
+            b16 = gpu_encode(p, items, W, out_dtype="bf16")["out"]
+            np.testing.assert_array_equal(b16, torch.from_numpy(got["out"]).bfloat16().float().numpy())
+        else:   # refused before anything is launched
+            with pytest.raises(eas.EasError) as ei:
+                gpu_encode(p, items, W, out_dtype="bf16")
+            assert ei.value.status == eas.EAS_ERR_UNSUPPORTED
 
 
 def test_mfma_rate_probe_reports_a_rate_within_the_clock_limit():
