@@ -265,7 +265,8 @@ struct PackArgs {
   int cu[kMaxSeqs + 1];
   int tchw[kMaxSeqs][4];
   const float* src[kMaxSeqs];
-  int strip0[kMaxSeqs + 1];   // set by launch_pack_vision: prefix sums of the requests' strips
+  int strip0[kMaxSeqs + 1];   // set by launch_pack_vision: prefix sums of the requests' strips,
+  int hw[kMaxSeqs][2];        // patch rows (pairs with the merger) and patch columns
 };
 hipError_t launch_pack_vision(const PackArgs& p, int cls, int merge, int patch, int tp, int K, int is_bf16,
                               void* packed, long total, hipStream_t s);

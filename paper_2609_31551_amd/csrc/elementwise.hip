@@ -260,59 +260,75 @@ __global__ void pack_vision_kernel(PackArgs p, int cls, int merge, int patch, in
 // bf16 packer: a block packs a strip of up to STRIP patches side by side (with the
 // merger, the two patch rows of its windows), whose token rows are consecutive in
 // storage order.  Consecutive threads read consecutive float2 pairs of an image row
-// (224 bytes a strip) and write them as bf16 into the block's LDS copy of the token
-// rows, which then leaves as one contiguous span of 8-byte writes.  Bound by memory;
-// with a thread per 14-pixel line instead, a wave's loads touched 64 lines each
-// (16 frames of 448 x 448: 45 -> 20 us, 2.9 TB/s; one 672 x 896 image 16 -> 12 us;
-// one 336 x 336 image 5.2 -> 5.6 us, its call unchanged).  Needs an even patch, even widths and 8-byte aligned sources.
-constexpr int STRIP = 4;
-__global__ __launch_bounds__(256) void pack_vision_vec_kernel(PackArgs p, int cls, int merge, int patch, int tp, int K,
-                                                              bf16* out) {
+// (224 bytes a strip of four) and write them as bf16 into the block's LDS copy of the
+// token rows, which then leaves as one contiguous span of 8-byte writes.  Bound by
+// memory, and by a block's own latency in small launches: so six loads a thread are in
+// flight at once, and the index arithmetic has two divisions.  Needs an even patch,
+// even widths and 8-byte aligned sources.  Kernel times (us), one thread a 14-pixel
+// line -> this: 224 x 224 image 4.9 -> 4.5, 336 x 504 7.5 -> 4.9, 672 x 896 15.0 ->
+// 8.6, 1344 x 1344 45.9 -> 17.4, 16 frames of 448 x 448 41.1 -> 13.7 (3.8 TB/s); 336 x
+// 336 images: one 4.4 -> 4.3, two 4.8 -> 5.0, 16 16.1 -> 10.4, 64 50.8 -> 29.1.
+template <int STRIP, int NT>
+__global__ __launch_bounds__(NT) void pack_vision_vec_kernel(PackArgs p, int cls, int merge, int patch, int tp, int C,
+                                                             int dy, int dc, int dtau, int K, bf16* out) {
   extern __shared__ __attribute__((aligned(16))) unsigned buf[];   // STRIP * merge token rows of K bf16
   const int r = find_seq(p.strip0, p.n, blockIdx.x);
-  const int H = p.tchw[r][2], W = p.tchw[r][3], C = p.tchw[r][1], h = H / patch, w = W / patch;
-  const int per_row = (w + STRIP - 1) / STRIP, rows_n = h / merge;   // strips a patch row, patch rows (pairs) a grid
-  const int q = blockIdx.x - p.strip0[r], ti = q / (per_row * rows_n), rq = q % (per_row * rows_n);
-  const int hi = rq / per_row * merge, wi = rq % per_row * STRIP, wp = min(STRIP, w - wi);
-  // 32 threads an image row of the strip (at most 4 * 8 float2 pairs), 8 rows at a time
-  const int hp = patch / 2, tx = threadIdx.x & 31, px = tx / hp, dx = tx - px * hp;
+  const int H = p.tchw[r][2], W = p.tchw[r][3], hr = p.hw[r][0], w = p.hw[r][1];
+  const int q = blockIdx.x - p.strip0[r], per_row = (w + STRIP - 1) / STRIP;
+  const int pr = q / per_row, ti = pr / hr, hi = (pr - ti * hr) * merge;
+  const int wi = (q - pr * per_row) * STRIP, wp = min(STRIP, w - wi);
+  // TR threads an image row of the strip (at most 8 float2 pairs a patch), RP rows at a time
+  constexpr int U = 6, TR = 8 * STRIP, RP = NT / TR;
+  const int hp = patch / 2, tx = threadIdx.x % TR;
+  int px = 0;
+#pragma unroll
+  for (int i = 1; i <= STRIP; ++i) px += tx >= i * hp;
+  const int dx = tx - px * hp;
   const bool on = px < wp;
   const int rows = merge * patch, nr = C * tp * rows;
   const int row2 = K / 2;                               // 4-byte words a token row
   const int tokx = merge == 2 ? (px >> 1) * 4 + (px & 1) : px;
   const float* base = p.src[r] + ((long)ti * tp * C * H + (long)hi * patch) * W + (long)wi * patch + (on ? 2 * tx : 0);
-  constexpr int U = 4;
-  for (int e0 = threadIdx.x >> 5; e0 < nr; e0 += U * 8) {
+  // the thread's image rows e, e + RP, ...: line y of channel c of frame tau, walked by
+  // additions (RP rows are dy lines, dc channels and dtau frames)
+  int e = threadIdx.x / TR, y = e, c = 0, tau = 0;
+  while (y >= rows) {
+    y -= rows;
+    if (++c == C) { c = 0; ++tau; }
+  }
+  for (; e < nr; e += U * RP) {
     float2 v[U];
     int dst[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int er = min(e0 + u * 8, nr - 1);           // past the end: the last row again
-      const int pl = er / rows, y = er - pl * rows, tau = pl / C, c = pl - tau * C;
+      const bool in = e + u * RP < nr;
       const int py = y >= patch ? 1 : 0;
-      v[u] = *reinterpret_cast<const float2*>(base + ((long)pl * H + y) * W);
-      dst[u] = (tokx + 2 * py) * row2 + ((c * tp + tau) * patch + y - py * patch) * hp + dx;
+      v[u] = *reinterpret_cast<const float2*>(base + (in ? ((long)(tau * C + c) * H + y) * W : 0));
+      dst[u] = in && on ? (tokx + 2 * py) * row2 + ((c * tp + tau) * patch + y - py * patch) * hp + dx : -1;
+      y += dy;
+      c += dc;
+      tau += dtau;
+      if (y >= rows) { y -= rows; ++c; }
+      if (c >= C) { c -= C; ++tau; }
     }
-    if (on) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        union { unsigned u; bf16 h[2]; } o;
-        o.h[0] = (bf16)v[u].x;
-        o.h[1] = (bf16)v[u].y;
-        buf[dst[u]] = o.u;
-      }
+    for (int u = 0; u < U; ++u) {
+      union { unsigned u; bf16 h[2]; } o;
+      o.h[0] = (bf16)v[u].x;
+      o.h[1] = (bf16)v[u].y;
+      if (dst[u] >= 0) buf[dst[u]] = o.u;
     }
   }
   __syncthreads();
   // first token of the strip: whole patch rows (or pairs) before it, then merge * wi tokens
-  const long tok0 = p.cu[r] + cls + ((long)ti * h + hi) * w + (long)merge * wi;
+  const long tok0 = p.cu[r] + cls + ((long)ti * hr * merge + hi) * w + (long)merge * wi;
   const int n8 = merge * wp * K / 4;   // 8-byte pieces (K % 4 == 0)
   uint2* o8 = reinterpret_cast<uint2*>(out + tok0 * K);
   const uint2* b8 = reinterpret_cast<const uint2*>(buf);
-  for (int i = threadIdx.x; i < n8; i += blockDim.x) o8[i] = b8[i];
+  for (int i = threadIdx.x; i < n8; i += NT) o8[i] = b8[i];
   if (cls && q == 0) {   // the request's CLS row
     uint2* c8 = reinterpret_cast<uint2*>(out + (long)p.cu[r] * K);
-    for (int i = threadIdx.x; i < K / 4; i += blockDim.x) c8[i] = make_uint2(0u, 0u);
+    for (int i = threadIdx.x; i < K / 4; i += NT) c8[i] = make_uint2(0u, 0u);
   }
 }
 
@@ -528,23 +544,49 @@ hipError_t launch_im2col_k3(const void* src, int frames_in, int C, int n_clips, 
   return hipGetLastError();
 }
 
+namespace {
+
+template <int STRIP, int NT>
+hipError_t launch_strips(PackArgs& q, int cls, int merge, int patch, int tp, int K, bf16* packed, hipStream_t s) {
+  q.strip0[0] = 0;
+  for (int r = 0; r < q.n; ++r)
+    q.strip0[r + 1] = q.strip0[r] + q.tchw[r][0] / tp * q.hw[r][0] * ((q.hw[r][1] + STRIP - 1) / STRIP);
+  constexpr int RP = NT / (8 * STRIP);
+  const int rows = merge * patch, C = q.tchw[0][1];
+  hipLaunchKernelGGL((pack_vision_vec_kernel<STRIP, NT>), dim3((unsigned)q.strip0[q.n]), dim3(NT),
+                     (size_t)STRIP * merge * K * 2, s, q, cls, merge, patch, tp, C, RP % rows, RP / rows % C,
+                     RP / rows / C, K, packed);
+  return hipGetLastError();
+}
+
+hipError_t launch_pack_strips(const PackArgs& p, int cls, int merge, int patch, int tp, int K, bf16* packed,
+                              hipStream_t s) {
+  PackArgs q = p;
+  long n4 = 0;   // strips of four patches
+  for (int r = 0; r < p.n; ++r) {
+    q.hw[r][0] = p.tchw[r][2] / patch / merge;
+    q.hw[r][1] = p.tchw[r][3] / patch;
+    n4 += (long)(p.tchw[r][0] / tp) * q.hw[r][0] * ((q.hw[r][1] + 3) / 4);
+  }
+  // Eight rows at a time cover one frame of patches without the merger (42 rows) in one
+  // round of loads; taller strips take 512 threads.  Those hold two patches while
+  // four-patch strips would give fewer than three blocks a CU (224 x 224: 4.5 us against
+  // 5.5; 1036 x 756, 518 strips of four: 9.8 against 10.3), and four past that
+  // (1344 x 1344, 1,152 strips: 17.4 us against 19.3).
+  if (K / patch * merge <= 48) return launch_strips<4, 256>(q, cls, merge, patch, tp, K, packed, s);
+  if (n4 < 3L * device_cus()) return launch_strips<2, 512>(q, cls, merge, patch, tp, K, packed, s);
+  return launch_strips<4, 512>(q, cls, merge, patch, tp, K, packed, s);
+}
+
+}  // namespace
+
 hipError_t launch_pack_vision(const PackArgs& p, int cls, int merge, int patch, int tp, int K, int is_bf16,
                               void* packed, long total, hipStream_t s) {
   if (total == 0) return hipSuccess;
   // with the merger every grid is even, so a strip holds whole windows
   bool vec = is_bf16 && patch % 2 == 0 && patch <= 16 && K / patch <= 256 && (uintptr_t)packed % 8 == 0 && merge <= 2;
   for (int r = 0; vec && r < p.n; ++r) vec = p.tchw[r][3] % 2 == 0 && (uintptr_t)p.src[r] % 8 == 0;
-  if (vec) {
-    PackArgs q = p;
-    q.strip0[0] = 0;
-    for (int r = 0; r < p.n; ++r) {
-      const int t = p.tchw[r][0] / tp, h = p.tchw[r][2] / patch, w = p.tchw[r][3] / patch;
-      q.strip0[r + 1] = q.strip0[r] + t * (h / merge) * ((w + STRIP - 1) / STRIP);
-    }
-    hipLaunchKernelGGL(pack_vision_vec_kernel, dim3((unsigned)q.strip0[p.n]), dim3(256), (size_t)STRIP * merge * K * 2,
-                       s, q, cls, merge, patch, tp, K, (bf16*)packed);
-    return hipGetLastError();
-  }
+  if (vec) return launch_pack_strips(p, cls, merge, patch, tp, K, (bf16*)packed, s);
   if (is_bf16)
     hipLaunchKernelGGL((pack_vision_kernel<bf16>), dim3(blocks_for(total, 256)), dim3(256), 0, s, p, cls, merge, patch,
                        tp, K, total, (bf16*)packed);

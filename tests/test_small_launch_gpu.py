@@ -84,3 +84,24 @@ def test_pack_strips(merge, tp):
     want, cu, _ = O.pack(p, items)
     np.testing.assert_array_equal(got["cu"], cu)
     np.testing.assert_array_equal(got["packed"].reshape(-1), np.asarray(want, np.float32).reshape(-1))
+
+
+@pytest.mark.parametrize("merge", [1, 2])
+def test_pack_strips_of_large_launches(merge):
+    """The tall strips' other width: two patches in small launches, four from three
+    blocks a CU on (here 1,152 strips and more), with an image that ends inside a
+    strip and one of a single patch (or window) a row beside it; exact."""
+    import torch
+    from oracle import encoder as O
+    from paper_2609_31551_amd import eas
+    d = 320
+    p = dict(C.with_layers(C.QWEN_IMAGE, 0), name="pack_large_m%d" % merge, hidden=d, heads=4, mlp=448, merge=merge,
+             out_dim=160 if merge == 2 else d)
+    for shapes in ([(2, 1344, 1316), (2, 84, 28 * merge // 2)], [(2, 336, 364)]):
+        items = synth.make_items(p, len(shapes), 0, shapes=shapes)
+        enc = eas.Encoder(p, max_tokens=1 << 14)
+        got, cu, _ = enc.pack_microbatch([torch.from_numpy(a).cuda() for a in items])
+        want, want_cu, _ = O.pack(p, items)
+        np.testing.assert_array_equal(cu, want_cu)
+        np.testing.assert_array_equal(got.float().cpu().numpy(), np.asarray(want, np.float32).reshape(-1))
+        enc.close()
