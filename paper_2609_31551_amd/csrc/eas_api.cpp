@@ -533,8 +533,8 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
   probe.qkv = ws.qkv;
   probe.ldqkv = 3 * d;
   probe.hd = hd;
-  const int qt = bf && attention_dma_supported(probe, N) ? attention_dma_q_tile(hd, cu_seqlens, n_seqs)
-                                                        : attention_q_tile(bf);
+  const bool dma = bf && attention_dma_supported(probe, N);
+  const int qt = dma ? attention_dma_q_tile(hd, cu_seqlens, n_seqs) : attention_q_tile(bf);
   work.qt = qt;
   int tiles = 0;
   double attn_flops = 0.0;
@@ -667,7 +667,7 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
     // LayerNorm kernels instead, which it lengthens: about half of that.
     aa.ahead = nullptr;
     aa.ahead_bytes = 0;
-    if (bf && !enc->halves && N <= kAheadTokens) {
+    if (dma && !enc->halves && N <= kAheadTokens) {
       const int64_t from = enc->layout.off(p + "o.w");
       const int64_t to = l + 1 < c.layers ? enc->layout.off("layers." + std::to_string(l + 1) + ".qkv.b")
                          : c.merge == 2   ? enc->layout.off("m2.b")
@@ -675,7 +675,8 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
       aa.ahead = static_cast<const char*>(weights) + from;
       aa.ahead_bytes = (long)(to - from);
     }
-    EAS_TRY(run(enc, s, attn_flops, (double)N * 4 * d * el, [&](const char** kn) {
+    // the record's bytes and time include the weights read ahead
+    EAS_TRY(run(enc, s, attn_flops, (double)N * 4 * d * el + (double)aa.ahead_bytes, [&](const char** kn) {
       return bf ? launch_attention_bf16(aa, work, tiles, N, s, kn) : launch_attention_f32(aa, work, tiles, s, kn);
     }));
     GemmArgs go = gemm_args(N, d, d, ws.ao, d, W(p + "o.w"), d, ws.x, d, 1);

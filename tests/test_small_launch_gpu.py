@@ -105,3 +105,42 @@ def test_pack_strips_of_large_launches(merge):
         np.testing.assert_array_equal(cu, want_cu)
         np.testing.assert_array_equal(got.float().cpu().numpy(), np.asarray(want, np.float32).reshape(-1))
         enc.close()
+
+
+def _attention_bytes(p, n):
+    """Recorded bytes of all attention launches of one call, less the activations', and
+    the weight spans between each layer's attention and the next (or the call's end)."""
+    import torch
+    from paper_2609_31551_amd import eas
+    cfg = eas.make_config(p, 1 << 15)
+    layout, total = eas.weights_layout(cfg)
+    off = {name: o for name, o, _ in layout}
+    last = "layers.%d." % (p["layers"] - 1)
+    spans = [off["layers.%d.qkv.b" % (i + 1)] - off["layers.%d.o.w" % i] for i in range(p["layers"] - 1)]
+    spans.append(off["m2.b" if p["merge"] == 2 else last + "fc2.b"] - off[last + "o.w"])
+    enc = eas.Encoder(p, 1 << 15)
+    side = 336 if p["kind"] == C.KIND_VIT_CLS_ABS else 280
+    items = [torch.rand((p["temporal_patch"], 3, side, side), device="cuda") for _ in range(n)]
+    packed, cu, grid = enc.pack_microbatch(items)
+    enc.profile_read()
+    enc.profile_enable(True)
+    enc.encode_microbatch(packed, cu, grid, torch.zeros(total, dtype=torch.uint8, device="cuda"))
+    torch.cuda.synchronize()
+    prof = enc.profile_read()
+    enc.close()
+    moved = sum(v["bytes"] for k, v in prof.items() if k.startswith("attn_"))
+    return moved - p["layers"] * int(cu[-1]) * 4 * p["hidden"] * 2, spans
+
+
+@pytest.mark.parametrize("preset", [C.CLIP_L336, C.QWEN_IMAGE])
+def test_attention_records_the_weights_it_reads_ahead(preset):
+    """The weights up to the next layer's q | k | v (the last layer: up to its FC2's end
+    here) are the attention launch's bytes; an attention kernel that reads none ahead
+    (head_dim 128) records none."""
+    p = dict(C.with_layers(preset, 2), merge=1, out_dim=preset["hidden"])
+    ahead, spans = _attention_bytes(p, 1)
+    assert ahead == sum(spans)
+    p.update(heads=preset["hidden"] // 128, head_dim=128)
+    if preset["kind"] == C.KIND_VIT_ROPE:
+        p["rope_sections"] = (0, 32, 32)
+    assert _attention_bytes(p, 1)[0] == 0
