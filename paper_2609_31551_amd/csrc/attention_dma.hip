@@ -411,16 +411,18 @@ void attn_bf16_dma_kernel(AttnArgs a, AttnWork w, int work_blocks) {
   }
 }
 
+// Attention blocks of 32 queries a wave in three quarters of the chip's wave slots (16 a CU)
+bool fills_chip(int blocks, int qt) { return (long)blocks * (qt / 32) > 12L * device_cus(); }
+
 template <int HD, int QB, int QT>
 hipError_t launch_hd(const AttnArgs& a, const AttnWork& w, int total_tiles, hipStream_t s) {
   using C = AttnCfg<HD, QB, QT>;
   constexpr int lds = 2 * C::BUF;
   const int work_blocks = total_tiles * a.heads;
   int ahead_blocks = 0;
-  if (a.ahead) {
+  if (a.ahead_bytes > 0) {
     const long lines = (a.ahead_bytes + 127) / 128;
-    const bool full = work_blocks * C::NW > 12L * device_cus();   // three quarters of its 16 waves a CU
-    const long threads = full ? (lines + AHEAD_BURST - 1) / AHEAD_BURST : AHEAD_THREADS;
+    const long threads = fills_chip(work_blocks, QT) ? (lines + AHEAD_BURST - 1) / AHEAD_BURST : AHEAD_THREADS;
     ahead_blocks = (int)((threads + 64 * C::NW - 1) / (64 * C::NW));
   }
   hipLaunchKernelGGL((attn_bf16_dma_kernel<HD, QB, QT>), dim3((unsigned)(work_blocks + ahead_blocks)),
@@ -446,6 +448,22 @@ int attention_dma_q_tile(int hd, const int* cu, int n) {
     s256 += (L + 255) / 256 * 256;
   }
   return s256 * 100 <= s128 * 102 ? 256 : 128;
+}
+
+// Of a span of `bytes` weight bytes, how many the launch of `blocks` attention blocks
+// reads ahead: all or none.  The paced reads of a long span outlast the attention
+// blocks (1,731 rows, 100 MB a layer: 20 -> 42 us a launch), and behind a launch that
+// fills the chip they take their own time while the GEMMs that follow are long enough
+// to wait for nothing.  Eight layers, read against not read: 39 MB (one to eight images,
+// hidden 1280) 1-11% faster, 57 MB (1536) 2% slower to 5% faster, 77 MB (1664) 4% slower
+// to 1% faster, 100 MB (2048) 2-8% slower; four layers of 300 MB 2-19% slower, and
+// slower than without any read-ahead before it (two images 2202 -> 2394 us; now 2049).
+// A Qwen-style merger's span, 118 MB once a call, whose GEMMs have a quarter of the
+// rows: images under 1,000 tokens 1-3% slower with it, 5,776 tokens, which fill the chip,
+// 0.9% faster.
+long attention_dma_ahead(int blocks, int qt, long bytes, bool merger) {
+  const long most = merger && fills_chip(blocks, qt) ? 128l << 20 : 64l << 20;
+  return bytes <= most ? bytes : 0;
 }
 
 bool attention_dma_supported(const AttnArgs& a, int N) {

@@ -224,7 +224,7 @@ struct AttnArgs {
   int heads, hd;
   float scale;                     // 1 / sqrt(hd)
   // Weights of the launches that follow, [ahead, ahead + ahead_bytes), which the
-  // DMA kernel's extra blocks pull into the last-level cache, or null
+  // DMA kernel's extra blocks pull into the last-level cache (ahead_bytes 0: none)
   const char* ahead; long ahead_bytes;
 };
 hipError_t launch_attention_bf16(const AttnArgs& a, const AttnWork& w, int total_tiles, int N, hipStream_t s,
@@ -233,6 +233,7 @@ hipError_t launch_attention_bf16(const AttnArgs& a, const AttnWork& w, int total
 // the sequences of a micro-batch (cu: n + 1 prefix sums)
 bool attention_dma_supported(const AttnArgs& a, int N);
 int attention_dma_q_tile(int hd, const int* cu, int n);
+long attention_dma_ahead(int blocks, int qt, long bytes, bool merger);
 hipError_t launch_attention_bf16_dma(const AttnArgs& a, const AttnWork& w, int total_tiles, hipStream_t s,
                                      const char** kname);
 hipError_t launch_attention_f32(const AttnArgs& a, const AttnWork& w, int total_tiles, hipStream_t s,

@@ -661,10 +661,11 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
     // cache, so a small micro-batch's GEMMs wait on HBM for them.  The attention
     // kernel, which leaves HBM and many CUs idle, reads ahead those of the launches
     // that follow it, up to the next layer's q | k | v (or the merger's): one
-    // contiguous span of the weight buffer.  Five CLIP images 1106 -> 1036 us, one
-    // audio clip 1082 -> 1023, one 3,072-token image 2009 -> 1938 (eight layers), one
-    // 8,192-token clip 3216 -> 3150 (four), one CLIP image unchanged.  Read in the
-    // LayerNorm kernels instead, which it lengthens: about half of that.
+    // contiguous span of the weight buffer, as far as the launch covers it.  Against
+    // none: one CLIP image 1663 -> 1580 us, one audio clip 4342 -> 4104 (whole
+    // encoders), five CLIP images 1122 -> 1058, one 3,072-token image 2137 -> 2047
+    // (eight layers), one 8,192-token clip 3239 -> 3223 (four).  Read in the LayerNorm
+    // kernels instead, which it lengthens: about half of that.
     aa.ahead = nullptr;
     aa.ahead_bytes = 0;
     if (dma && !enc->halves && N <= kAheadTokens) {
@@ -673,7 +674,7 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
                          : c.merge == 2   ? enc->layout.off("m2.b")
                                           : enc->layout.off(p + "fc2.b");
       aa.ahead = static_cast<const char*>(weights) + from;
-      aa.ahead_bytes = (long)(to - from);
+      aa.ahead_bytes = attention_dma_ahead(tiles * H, qt, (long)(to - from), c.merge == 2 && l + 1 == c.layers);
     }
     // the record's bytes and time include the weights read ahead
     EAS_TRY(run(enc, s, attn_flops, (double)N * 4 * d * el + (double)aa.ahead_bytes, [&](const char** kn) {

@@ -144,3 +144,17 @@ def test_attention_records_the_weights_it_reads_ahead(preset):
     if preset["kind"] == C.KIND_VIT_ROPE:
         p["rope_sections"] = (0, 32, 32)
     assert _attention_bytes(p, 1)[0] == 0
+
+
+def test_attention_reads_no_long_spans_ahead():
+    """Weight spans over 64 MiB (hidden 2048: 101 and 76 MB here) are left, in small
+    launches and in those that fill the chip; the merger's (118 MB) is read only by the
+    latter."""
+    p = dict(C.with_layers(C.CLIP_L336, 2), name="clip_w2048", hidden=2048, heads=32, mlp=8192, out_dim=2048)
+    for n in (1, 8):
+        ahead, spans = _attention_bytes(p, n)
+        assert min(spans) > 64 << 20 and ahead == 0
+    p = C.with_layers(C.QWEN_IMAGE, 2)
+    ahead, spans = _attention_bytes(p, 1)
+    assert ahead == spans[0] <= 64 << 20 < spans[1]
+    assert _attention_bytes(p, 14)[0] == sum(spans)
