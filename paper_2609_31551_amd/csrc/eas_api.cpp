@@ -668,7 +668,7 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
     // kernels instead, which it lengthens: about half of that.
     aa.ahead = nullptr;
     aa.ahead_bytes = 0;
-    if (dma && !enc->halves && N <= kAheadTokens) {
+    if (dma && !enc->halves && N <= kAheadTokens && (uintptr_t)weights % 4 == 0) {   // read by dwords
       const int64_t from = enc->layout.off(p + "o.w");
       const int64_t to = l + 1 < c.layers ? enc->layout.off("layers." + std::to_string(l + 1) + ".qkv.b")
                          : c.merge == 2   ? enc->layout.off("m2.b")

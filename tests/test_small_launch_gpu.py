@@ -107,7 +107,7 @@ def test_pack_strips_of_large_launches(merge):
         enc.close()
 
 
-def _attention_bytes(p, n):
+def _attention_bytes(p, n, offset=0):
     """Recorded bytes of all attention launches of one call, less the activations', and
     the weight spans between each layer's attention and the next (or the call's end)."""
     import torch
@@ -124,7 +124,7 @@ def _attention_bytes(p, n):
     packed, cu, grid = enc.pack_microbatch(items)
     enc.profile_read()
     enc.profile_enable(True)
-    enc.encode_microbatch(packed, cu, grid, torch.zeros(total, dtype=torch.uint8, device="cuda"))
+    enc.encode_microbatch(packed, cu, grid, torch.zeros(offset + total, dtype=torch.uint8, device="cuda")[offset:])
     torch.cuda.synchronize()
     prof = enc.profile_read()
     enc.close()
@@ -158,3 +158,12 @@ def test_attention_reads_no_long_spans_ahead():
     ahead, spans = _attention_bytes(p, 1)
     assert ahead == spans[0] <= 64 << 20 < spans[1]
     assert _attention_bytes(p, 14)[0] == sum(spans)
+
+
+def test_attention_reads_nothing_ahead_of_unaligned_weights():
+    """Weights at an odd multiple of 2 bytes, which the encoder accepts, are not read by
+    dwords; at 4 bytes they are."""
+    p = C.with_layers(C.CLIP_L336, 1)
+    assert _attention_bytes(p, 1, offset=2)[0] == 0
+    ahead, spans = _attention_bytes(p, 1, offset=4)
+    assert ahead == sum(spans)
