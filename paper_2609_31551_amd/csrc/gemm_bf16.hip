@@ -1132,16 +1132,18 @@ bool tile_rows_fit(const GemmArgs& a) {
 
 // The persistent asynchronous-epilogue kernel: bias / activation epilogues, two
 // to 32 k-tiles.  Past that the epilogue is a small share of a tile and the
-// per-tile kernel measured slightly faster (both give the same bits).
+// per-tile kernel measured slightly faster (both give the same bits).  The bias row is
+// read by 16-byte DMA (the weights of a caller may lie at any 2-byte address, and the
+// padded patch weight beside its bias is the library's own, aligned copy).
 bool async_ok(const GemmArgs& a) {
-  return tile_ok(a) && tile_rows_fit(a) && !a.resid && !a.pos && a.K >= 2 * BK && a.K <= 32 * BK;
+  return tile_ok(a) && tile_rows_fit(a) && al16(a.bias) && !a.resid && !a.pos && a.K >= 2 * BK && a.K <= 32 * BK;
 }
 
 // Its residual form (fp32 residual stream, fp32 output: O-projection and FC2), any
 // K: the residual read and write are a large share of such a tile, and the
 // stores drain under the next tile's k-loop.
 bool async_res_ok(const GemmArgs& a) {
-  return tile_ok(a) && tile_rows_fit(a) && a.resid && a.out_f32 && !a.pos && a.K >= 2 * BK;
+  return tile_ok(a) && tile_rows_fit(a) && al16(a.bias) && a.resid && a.out_f32 && !a.pos && a.K >= 2 * BK;
 }
 
 }  // namespace

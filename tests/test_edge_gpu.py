@@ -12,6 +12,7 @@ library must refuse.
 * Encoders without a connector (merge == 1) other than the CLS model: the final
   residual stream is the output, in both output types; without layers the
   embedding is, and only fp32 output is accepted.
+* Weights at addresses that are multiples of 2 or 8 bytes only.
 """
 import numpy as np
 import pytest
@@ -97,6 +98,26 @@ def test_encoders_without_a_connector_write_the_residual_stream(kind, dtype):
             with pytest.raises(eas.EasError) as ei:
                 gpu_encode(p, items, W, out_dtype="bf16")
             assert ei.value.status == eas.EAS_ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("offset", [2, 8])
+@pytest.mark.parametrize("preset", [C.QWEN_IMAGE, C.CLIP_L336, C.WHISPER_L], ids=lambda p: p["name"])
+def test_weights_at_unaligned_addresses(preset, offset):
+    """No kernel reads such weights or biases by wider pieces than their address allows
+    (the patch GEMM runs on an aligned copy of its weight, its bias does not)."""
+    import torch
+    from paper_2609_31551_amd import eas
+    p = C.with_layers(preset, 1)
+    W = synth.make_weights(p, 0)
+    items = synth.make_items(p, 2, 0, shapes=[(2, 56, 84), (2, 280, 308)] if preset is C.QWEN_IMAGE else None)
+    ref = oracle_encode(p, items, W)
+    enc = eas.Encoder(p, max_tokens=int(ref["cu"][-1]), max_seqs=2)
+    wdev = eas.upload_weights(enc.cfg, W)
+    moved = torch.zeros(offset + wdev.numel(), dtype=torch.uint8, device="cuda")[offset:]
+    moved.copy_(wdev)
+    assert moved.data_ptr() % 16 == offset
+    print("[edge] %s, weights at 16 n + %d" % (p["name"], offset), flush=True)
+    check_parity(p, gpu_encode(p, items, W, enc=enc, wdev=moved), ref)
 
 
 def test_mfma_rate_probe_reports_a_rate_within_the_clock_limit():
