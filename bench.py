@@ -5,7 +5,9 @@ already resident in HBM: pack the raw requests into a padding-free batch, then
 run the encoder forward pass and connector (eas_pack_microbatch +
 eas_encode_microbatch).  The headline workload is a micro-batch of 64 CLIP
 ViT-L/14-336 images (577 tokens each, bf16 weights N(0, 0.02), pixels U[0,1),
-seed 0), the image workload of the paper's Table 3.  Prints ONE JSON line.
+seed 0), the image workload of the paper's Table 3.  Prints ONE short JSON line:
+the headline, its roofline and the swept throughputs; the whole record (kernel
+tables, serving, capacity, reference timings) goes to the file of --details.
 
 Besides the headline, every workload of the evaluation (Section 4.1) is swept
 over micro-batch sizes on a fixed pool of requests: a pass walks the whole
@@ -62,6 +64,7 @@ def parse():
     ap.add_argument("--colocation", default="",
                     help="micro-batch sizes of a co-location profile of the headline preset: encode latency "
                          "with 12.5/30/50/70/90%% of the CUs and the smallest-safe-share table ('' to skip)")
+    ap.add_argument("--details", default="", help="file to write the whole record to (JSON)")
     ap.add_argument("--copy-calib-mib", type=int, default=0,
                     help="only run a plain device copy of this many MiB (HBM counter calibration)")
     return ap.parse_args()
@@ -493,6 +496,33 @@ def serving(wl, rows, load, live_s, B=64, p=0.6, max_age=1.0):
     return out
 
 
+LINE_MAX = 2000   # characters a reader of the output's end can count on
+
+
+def headline(result):
+    """The printed part of the record: every field up to the kernel tables, numbers to
+    five digits but for the headline's own, sweeps as micro-batch -> [tokens/s, items/s]."""
+    def short(v):
+        if isinstance(v, float):
+            return float("%.5g" % v)
+        return {k: short(x) for k, x in v.items()} if isinstance(v, dict) else v
+    line = {k: result[k] for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step",
+                                   "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config")}
+    for k in ("images_per_s", "roofline", "gemm_attn_mfma_frac"):
+        if k in result:
+            line[k] = short(result[k])
+    if "cpu_baseline" in result:
+        line["cpu_baseline"] = short({k: result["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind")})
+    if "workloads" in result:
+        line["sweep"] = {name: {str(r["micro_batch"]): [round(r["tokens_per_s"]), short(r["items_per_s"])]
+                                for r in w["sweep"]} for name, w in result["workloads"].items()}
+    text = json.dumps(line)
+    if len(text) > LINE_MAX:   # more sizes swept than fit: the headline alone
+        line.pop("sweep", None)
+        text = json.dumps(line)
+    return text
+
+
 def parse_workloads(spec):
     out = []
     for part in spec.split(";"):
@@ -599,7 +629,10 @@ def main():
         result["workloads"] = workloads
     if cpu_configs:
         result["cpu_configs"] = cpu_configs
-    print(json.dumps(result), flush=True)
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(result, f, indent=1)
+    print(headline(result), flush=True)
 
 
 if __name__ == "__main__":
