@@ -3,7 +3,9 @@ deep-pipelined bf16 GEMM (64 x 64 to 192 x 128 tiles, steps of 64 or 128 k) and
 the fp32 GEMM's 16 x 16 tiles with their own LayerNorm statistics.  Every kernel
 sums k in the same order, so a request alone must equal the same request inside a
 micro-batch that takes the persistent kernels (or the 64 x 64 fp32 tiles) bit
-for bit; the request alone is also checked against the float64 reference."""
+for bit; the request alone is also checked against the float64 reference.
+Besides: the vision packer's strips, and the weights that the attention launches of
+such calls read ahead."""
 import numpy as np
 import pytest
 
@@ -13,8 +15,8 @@ from paper_2609_31551_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# (patch rows, patch columns): 4 to 580 tokens, one merge window around the edges
-# of 64, 128 and 192 rows, and one and two tiles per CU of the column counts
+# (patch rows, patch columns): 4 to 580 tokens, one merge window around multiples of 64
+# rows; nearly all of their GEMMs take the 64 x 64 tiles
 GRIDS = [(2, 2), (2, 30), (8, 8), (2, 34), (2, 62), (8, 16), (2, 66), (2, 94), (12, 16), (14, 14), (2, 290)]
 
 
@@ -34,16 +36,72 @@ def _alone_and_batched(p, grids, rest):
 
 
 def test_deep_gemm_tile_edges():
-    """1280 / 5120 / 3584 columns, k of 1216 (steps of 64), 1280 and 5120 (of 128);
-    the batch of 9,000 more tokens runs as two halves on the persistent kernels."""
+    """The row edges of the 64 x 64 tiles in a real width: 1280 / 5120 / 3584 columns, k
+    of 1216 (steps of 64), 1280 and 5120 (of 128); the batch of 9,000 more tokens runs
+    as two halves on the persistent kernels."""
     _alone_and_batched(C.with_layers(C.QWEN_IMAGE, 1), GRIDS, [(48, 48)] * 4)
 
 
 def test_deep_gemm_odd_widths():
-    """A hidden width that ends inside every column tile (320 = 2 x 128 + 64, k of five
-    64-steps: no 128-steps) and a 160-wide output."""
+    """The 64 x 64 tiles with k of five and seven 64-steps (no 128-steps) and a 160-wide
+    output, which ends inside a column tile."""
     p = dict(C.with_layers(C.QWEN_IMAGE, 2), name="qwen_w320", hidden=320, heads=4, mlp=448, out_dim=160)
     _alone_and_batched(p, GRIDS, [(48, 48)] * 4)
+
+
+# A one-layer rotary encoder without a connector, one request of h x w patches alone:
+# (hidden, head_dim, mlp, (h, w)), and which of its GEMMs -- patch (k 1216, fp32 output),
+# qkv (rotary epilogue), o (fp32 residual), fc1, fc2 (residual; with bf16 output its last
+# form) -- each deep tile runs.  All end inside a row tile; hidden 320 and 1728 (and three
+# times them) end 64 columns into a 128-wide tile, mlp 328, 3848 and 4104 8 columns into a
+# wave's 32, and the other hidden widths 16 into them (their qkv, o and fc1, whose k is
+# no multiple of 64, take another kernel).
+FORMS = [
+    (320, 80, 328, (9, 11), {"64x64": ("patch", "qkv", "o", "fc1")}),
+    (400, 80, 512, (5, 7), {"64x64": ("patch", "fc2")}),                        # steps of 128 k
+    (400, 80, 128, (61, 63), {"64x64": ("fc2",), "64x128": ("patch",)}),        # one step of 128 k; 427 tiles
+    (880, 80, 128, (33, 35), {"64x128": ("patch", "fc2")}),
+    (320, 80, 328, (45, 47), {"64x64": ("patch", "o", "fc1"), "128x128": ("qkv",)}),
+    (320, 80, 4104, (21, 23), {"64x64": ("patch", "qkv", "o"), "128x128": ("fc1",)}),
+    (720, 80, 512, (51, 53), {"128x128": ("patch", "fc2")}),
+    (320, 80, 4104, (29, 31), {"64x64": ("patch", "qkv", "o"), "192x128": ("fc1",)}),
+    (320, 80, 328, (65, 67), {"64x128": ("patch", "o", "fc1"), "192x128": ("qkv",)}),
+    (1040, 80, 1280, (59, 61), {"192x128": ("patch", "fc2")}),
+    (1728, 64, 3848, (45, 47), {"128x128": ("patch", "o"), "192x128": ("qkv", "fc1")}),   # 451 and 341 tiles
+    (1840, 80, 2560, (65, 67), {"192x128": ("fc2",)}),                          # 345 tiles
+]
+
+
+@pytest.mark.parametrize("d,hd,mlp,grid,tiles", FORMS, ids=["%d_%d_%dx%d" % (f[0], f[2], *f[3]) for f in FORMS])
+def test_deep_gemm_forms(d, hd, mlp, grid, tiles):
+    """Every deep tile with remainders of rows and columns in each epilogue, one and two
+    rounds of tiles; the profile's flops say which launches took which tile (on a
+    256-CU device, whose count the choice depends on)."""
+    import torch
+    from paper_2609_31551_amd import eas
+    p = dict(C.with_layers(C.QWEN_IMAGE, 1), name="deep_%d_%d" % (d, mlp), hidden=d, heads=d // hd, head_dim=hd, mlp=mlp,
+             merge=1, out_dim=d, rope_sections=(0, hd // 4, hd // 4))
+    W = synth.make_weights(p, 0)
+    shapes = [(2, 14 * h, 14 * w) for h, w in [grid] + [(48, 48)] * 4]
+    items = synth.make_items(p, len(shapes), 0, shapes=shapes)
+    m = grid[0] * grid[1]
+    enc = eas.Encoder(p, max_tokens=m + 4 * 48 * 48, max_seqs=len(items))
+    wdev = eas.upload_weights(enc.cfg, W)
+    print("[small] %s: %d tokens alone" % (p["name"], m), flush=True)
+    enc.profile_enable(True)
+    alone = gpu_encode(p, items[:1], W, enc=enc, wdev=wdev)
+    enc.profile_enable(False)
+    prof = enc.profile_read()
+    nk = {"patch": (d, 1216), "qkv": (3 * d, d), "o": (d, d), "fc1": (mlp, d), "fc2": (d, mlp)}
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        want = {"gemm_bf16_deep_" + t: sum(2.0 * m * nk[g][0] * nk[g][1] for g in gs) for t, gs in tiles.items()}
+        assert {k: v["flops"] for k, v in prof.items() if k.startswith("gemm_bf16_deep_")} == want
+    e = rel_err(alone["out"], oracle_encode(p, items[:1], W)["out"])
+    assert e <= TOL[p["dtype"]], e
+    batch = gpu_encode(p, items, W, enc=enc, wdev=wdev)
+    np.testing.assert_array_equal(alone["out"], batch["out"][:m])
+    b16 = gpu_encode(p, items[:1], W, out_dtype="bf16", wdev=wdev)
+    np.testing.assert_array_equal(b16["out"], torch.from_numpy(alone["out"]).bfloat16().float().numpy())
 
 
 def test_cls_model_bf16_output_small():
