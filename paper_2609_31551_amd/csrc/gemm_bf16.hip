@@ -11,7 +11,7 @@
 //    chunk) assignment applies an XOR swizzle (chunk ^ ((row >> 1) & 7)) that
 //    spreads the MFMA operand reads -- 32 rows at one k offset, 16 lanes per
 //    LDS cycle over 64 banks -- without conflicts.
-//  * ST LDS stages of 64 k: tile k+ST-1 streams in while tile k is consumed
+//  * Two LDS stages of 64 k: tile k+1 streams in while tile k is consumed
 //    (launches of about one tile per CU run the deep-pipelined kernel below
 //    instead).  The DMA is issued from inline assembly so the compiler does
 //    not serialise it against the LDS reads; completion is tracked with
@@ -70,7 +70,7 @@ template <int N> __device__ __forceinline__ void wait_vm() {
 }
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-template <int BM, int BN, int WGM, int WGN, int ST = 2>
+template <int BM, int BN, int WGM, int WGN>
 struct Cfg {
   static constexpr int NW = WGM * WGN, NT = 64 * NW;
   static constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -81,9 +81,9 @@ struct Cfg {
   static constexpr int DA = BM / RPI / NW, DB = BN / RPI / NW;   // DMA instructions per wave per stage
   static constexpr int DPS = DA + DB;
   static constexpr int SLD = WN + 4;                            // epilogue slab row (floats)
-  static constexpr int LDS = ST * STAGE > NW * 32 * SLD * 4 ? ST * STAGE : NW * 32 * SLD * 4;
+  static constexpr int LDS = 2 * STAGE > NW * 32 * SLD * 4 ? 2 * STAGE : NW * 32 * SLD * 4;
   static_assert(BM % (RPI * NW) == 0 && BN % (RPI * NW) == 0, "DMA split");
-  static_assert(DPS * (ST - 1) < 64, "vmcnt range");
+  static_assert(DPS < 64, "vmcnt range");
   // conflict-free chunk swizzle for 128-byte rows: 16 rows per LDS cycle hit 16 distinct 16-byte slots
   __device__ static int sw(int row) { return (row >> 1) & 7; }
 };
@@ -117,9 +117,9 @@ __device__ __forceinline__ void wait_tiles(int n) {
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int ST>
+template <int BM, int BN, int WGM, int WGN>
 __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_tile_kernel(GemmArgs a) {
-  using C = Cfg<BM, BN, WGM, WGN, ST>;
+  using C = Cfg<BM, BN, WGM, WGN>;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const unsigned lds0 = (unsigned)(size_t)((__attribute__((address_space(3))) char*)smem);
   const int tid = threadIdx.x, lane = tid & 63;
@@ -209,38 +209,41 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_tile_kernel(GemmArgs
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  // prologue: tiles 0 .. ST-1 in flight; wait for tile 0
-#pragma unroll
-  for (int s = 0; s < ST; ++s)
-    if (s < KT) issue(s, s);
-  wait_tiles<C::DPS, ST - 1>(min(ST, KT) - 1);
+  // prologue: tiles 0 and 1 in flight; wait for tile 0
+  issue(0, 0);
+  if (KT > 1) {
+    issue(1, 1);
+    wait_vm<C::DPS>();
+  } else {
+    wait_vm<0>();
+  }
   __syncthreads();
   load_frags(0, cofs[0], fa[0], fb[0]);
 
   // every k-tile but the last; the loop body has no branch around its MFMAs,
   // so the next tile's first fragment reads interleave with this tile's last slice
   for (int kt = 0; kt < KT - 1; ++kt) {
-    const int st = kt % ST;
+    const int st = kt & 1;
 #pragma unroll
     for (int h = 0; h < NH - 1; ++h) {
       load_frags(st, cofs[h + 1], fa[(h + 1) & 1], fb[(h + 1) & 1]);
       mma(fa[h & 1], fb[h & 1]);
       interleave();
     }
-    // this wave's reads of stage st are done once lgkmcnt drains; tile kt+1
-    // has landed once only the tiles after it (up to kt+ST-1) are in flight;
-    // after the barrier every wave is past stage st, refilled with tile kt+ST
+    // this wave's reads of stage st are done once lgkmcnt drains, and tile kt+1, the
+    // only one in flight, has landed; after the barrier every wave is past stage st,
+    // refilled with tile kt+2
     wait_lds();
-    wait_tiles<C::DPS, ST - 2>(min(ST - 2, KT - 2 - kt));
+    wait_vm<0>();
     __builtin_amdgcn_s_barrier();
-    if (kt + ST < KT) issue(kt + ST, st);
+    if (kt + 2 < KT) issue(kt + 2, st);
     __builtin_amdgcn_sched_barrier(0);
-    load_frags((kt + 1) % ST, cofs[0], fa[NH & 1], fb[NH & 1]);
+    load_frags(st ^ 1, cofs[0], fa[NH & 1], fb[NH & 1]);
     mma(fa[(NH - 1) & 1], fb[(NH - 1) & 1]);
     interleave();
   }
   {
-    const int st = (KT - 1) % ST;
+    const int st = (KT - 1) & 1;
 #pragma unroll
     for (int h = 0; h < NH - 1; ++h) {
       load_frags(st, cofs[h + 1], fa[(h + 1) & 1], fb[(h + 1) & 1]);
@@ -1037,18 +1040,18 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_async_kernel(GemmArg
   }
 }
 
-template <int BM, int BN, int WGM, int WGN, int ST = 2>
+template <int BM, int BN, int WGM, int WGN>
 hipError_t launch_tile(const GemmArgs& a, hipStream_t s) {
-  using C = Cfg<BM, BN, WGM, WGN, ST>;
+  using C = Cfg<BM, BN, WGM, WGN>;
   static bool attr = false;   // raise the dynamic-LDS limit once per instantiation
   if (!attr) {
-    const hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_tile_kernel<BM, BN, WGM, WGN, ST>,
+    const hipError_t e = hipFuncSetAttribute((const void*)gemm_bf16_tile_kernel<BM, BN, WGM, WGN>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     if (e != hipSuccess) return e;
     attr = true;
   }
   const long tiles = (long)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_bf16_tile_kernel<BM, BN, WGM, WGN, ST>), dim3((unsigned)tiles), dim3(C::NT), C::LDS, s, a);
+  hipLaunchKernelGGL((gemm_bf16_tile_kernel<BM, BN, WGM, WGN>), dim3((unsigned)tiles), dim3(C::NT), C::LDS, s, a);
   return hipGetLastError();
 }
 
