@@ -491,6 +491,8 @@ namespace {
 
 // One-pass calls read the next launches' weights ahead (below) up to this many
 // tokens; past it, or in two halves, a layer's weights are a small share of its time.
+// Read against not read (four layers): a clip of 6,144 tokens 1.7% faster, 8,192
+// 0.5%, 9,216 - 24,576 within 0.7% either way.
 constexpr int kAheadTokens = 16384;
 
 // One encode pass over requests cu_seqlens[0 .. n_seqs] (offsets from this

@@ -44,14 +44,19 @@ namespace {
 
 constexpr int BK = 64;
 constexpr int kResAhead = 1;
-// Buffer-store cache policies of the bf16 outputs.  Written through (SC1), an output
-// leaves as fast as a non-temporal one and is still in the last-level cache when the
-// next kernel reads it: FC1 + FC2 of five images 68.0 -> 60.0 us, of one 3,072-token
-// image 91.8 -> 79.7, with the weights in that cache too.  An output that would push
-// the rest out of the 256 MB cache goes non-temporal: over 84 MB (an 8,192-token
-// clip, 84 MB: written through 1.1% faster; 64 images in one pass, 302 MB: slower), or
-// over 64 MB for each of two halves side by side (16 images, 38 MB a half: 3.4%
-// faster; 24, 57 MB: 1.4% faster; 48, 85 MB: 0.6% slower; 64, 151 MB: 1.6% slower).
+// Buffer-store cache policies.  Written through (SC1), an output leaves as fast as a
+// non-temporal one and is still in the last-level cache when the next kernel reads it:
+// FC1 + FC2 of five images 68.0 -> 60.0 us, of one 3,072-token image 91.8 -> 79.7, with
+// the weights in that cache too.  The deep kernel writes all its outputs through (they
+// are small), the persistent kernel its bf16 outputs up to 84 MiB a launch, or 64 MiB
+// beside another half's launches; the rest, which would push everything else out of the
+// 256 MB cache, go non-temporal.  A product in head and tail launches is decided for
+// each: decided by the whole product, 24 - 64 images, 6 - 24 audio clips and two to
+// four video clips measured equal.  Against non-temporal, by the size of FC1's output
+// (MB = 10^6 bytes): one pass, 84 MB (an 8,192-token clip) 1.4% faster, 94 - 126 MB 0.3
+// - 1.8% faster, 147 - 252 MB equal, so the limit is on the safe side; each of two
+// halves, 38 MB (16 images) 4.3% faster, 57 and 66 MB 1 - 2.6%, 76 - 95 MB equal, 113
+// MB 0.5 - 0.9% slower, 132 and 151 MB (56 and 64 images) 1.8% slower.
 constexpr int kStoreNT = 2, kStoreThrough = 16;
 constexpr long kThroughBytes = 84l << 20, kThroughBytesShared = 64l << 20;
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -355,8 +360,10 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_tile_kernel(GemmArgs
 //  * a step's DMA instructions are spread over its slices: issued in one block they
 //    hold up the MFMAs behind a full vector memory queue (128 x 128 tiles: 8%);
 //  * 64 x 64 tiles step by 128 k (KS = 2): half the barriers (0.22 -> 0.18 us per 64 k);
-//  * bias, residual and positions are fetched before the first operands, and the
-//    epilogue writes whole 128-byte rows through LDS (1.0 - 1.5 us per launch).
+//  * the bias row, the fp32 form's residual and the rotary positions are fetched before
+//    the first operands (a position table's rows, and the residual of a bf16 output,
+//    once a call each, in the epilogue), and the epilogue writes whole 128-byte rows
+//    through LDS (1.0 - 1.5 us per launch).
 // One image (577 rows): O-projection 9.6 -> 6.9 us, FC2 23.4 -> 15.8, QKV 11.5 ->
 // 9.4, FC1 14.9 -> 12.0; five images' O-projection 17.7 -> 14.0, FC2 41.5 -> 33.2
 // (back-to-back launches, weights changing).  What is left over the DMA time is
@@ -460,11 +467,11 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_deep_kernel(GemmArgs
     __builtin_amdgcn_sched_barrier(0);
   };
 
-  // What the epilogue reads besides the sums is fetched before the operands (it
-  // lands first): the lane's bias values and, with a residual, its values of
-  // every block.  Ordinary loads, which the compiler waits for by itself at
-  // their use; by then no DMA is in flight.  Columns past N are clamped or out
-  // of the buffer's range, rows past M out of range.
+  // Fetched before the operands (so landing first): the lane's bias values, with fp32
+  // output and a residual its values of every block, and the rows' rotary positions.
+  // Ordinary loads, which the compiler waits for by itself at their use; by then no
+  // DMA is in flight.  Columns past N are clamped or out of the buffer's range, rows
+  // past M clamped or out of range.
   const int rows = min(BM, a.M - m0);
   const int prow = lane >> 3, pc = (lane & 7) * 4;   // fp32: eight lanes a 128-byte row of a 32 x 32 block
   uint2 bq[C::FN][OUTF32 ? 1 : 4];
@@ -619,7 +626,7 @@ __global__ __launch_bounds__(64 * WGM * WGN) void gemm_bf16_deep_kernel(GemmArgs
               rope_rotate(v[2], v[3], rope_turns(a, i0 + 1, rp[i].x, rp[i].y, rp[i].z));
             }
           }
-if (a.resid) {   // one launch a call (a CLS model's last layer with bf16 output)
+          if (a.resid) {   // one launch a call (the last FC2 of an encoder without a connector)
             const long ri = (long)min(m0 + wm * C::WM + i * 32 + lrow, a.M - 1) * a.ldr;
             const int n = min(n0 + wn * C::WN + j * 32 + 8 * q + 4 * g, a.N - 4);
             const float4 t = *reinterpret_cast<const float4*>(a.resid + ri + n);
@@ -1066,14 +1073,15 @@ hipError_t launch_deep_t(const GemmArgs& a, hipStream_t s) {
     attr = true;
   }
   const long tiles = (long)((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN);
-  hipLaunchKernelGGL((gemm_bf16_deep_kernel<BM, BN, WGM, WGN, ST, KS, OUTF32>), dim3((unsigned)tiles), dim3(C::NT), C::LDS, s,
-                     a);
+  hipLaunchKernelGGL((gemm_bf16_deep_kernel<BM, BN, WGM, WGN, ST, KS, OUTF32>), dim3((unsigned)tiles), dim3(C::NT),
+                     C::LDS, s, a);
   return hipGetLastError();
 }
 
 template <int BM, int BN, int WGM, int WGN, int ST, int KS>
 hipError_t launch_deep(const GemmArgs& a, hipStream_t s) {
-  return a.out_f32 ? launch_deep_t<BM, BN, WGM, WGN, ST, KS, 1>(a, s) : launch_deep_t<BM, BN, WGM, WGN, ST, KS, 0>(a, s);
+  return a.out_f32 ? launch_deep_t<BM, BN, WGM, WGN, ST, KS, 1>(a, s)
+                   : launch_deep_t<BM, BN, WGM, WGN, ST, KS, 0>(a, s);
 }
 
 template <int BM, int BN, int WGM, int WGN, int OUTF32, int RES, int ROPE, int THROUGH>
@@ -1102,7 +1110,8 @@ hipError_t launch_async_k(const GemmArgs& a, hipStream_t s) {
 template <int BM, int BN, int WGM, int WGN, int OUTF32, int RES = 0, int ROPE = 0>
 hipError_t launch_async_t(const GemmArgs& a, hipStream_t s) {
   if constexpr (!OUTF32)
-    if ((long)a.M * a.N * 2 <= (a.shared ? kThroughBytesShared : kThroughBytes)) return launch_async_k<BM, BN, WGM, WGN, OUTF32, RES, ROPE, 1>(a, s);
+    if ((long)a.M * a.N * 2 <= (a.shared ? kThroughBytesShared : kThroughBytes))
+      return launch_async_k<BM, BN, WGM, WGN, OUTF32, RES, ROPE, 1>(a, s);
   return launch_async_k<BM, BN, WGM, WGN, OUTF32, RES, ROPE, 0>(a, s);
 }
 
@@ -1192,7 +1201,8 @@ int device_cus() {
   static int cus = 0;
   if (!cus) {
     int dev = 0, n = 0;
-    if (hipGetDevice(&dev) == hipSuccess && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)
       cus = n;
     else
       return 256;
@@ -1206,7 +1216,12 @@ namespace {
 // k_tiles * step * (1 + slope * n / CUs) + epilogue us, the epilogue growing with
 // the share of the chip that writes at once (and with a residual, which is read).
 // Fitted to back-to-back launches of the encoders' shapes (M = 577 - 4,616, N =
-// 1,024 - 5,120, K = 1,024 - 5,120), which it reproduces within 6%.
+// 1,024 - 5,120, K = 1,024 - 5,120), which it reproduces within 6%.  The CUs are the
+// device's: a reservation beside the encoder (eas_cu_reserve), which holds part of
+// them, is not seen here.  Beside one that leaves 12.5 - 90% of the CUs, one to 16
+// images, one to four audio clips and one video clip were as fast as with the kernels
+// before this one or faster (up to 34%), but for eight images on 70% of them, where
+// FC2's 200 tiles no longer fit one round: 1.5% slower.
 struct DeepOpt { const char* name; int bm, bn; double step, slope, e0, e1, r1; };
 constexpr DeepOpt kDeep[4] = {{"gemm_bf16_deep_64x64", 64, 64, 0.165, 0.20, 0.8, 1.2, 1.2},
                               {"gemm_bf16_deep_64x128", 64, 128, 0.237, 0.34, 1.1, 0.8, 2.8},
@@ -1231,7 +1246,9 @@ double deep_time(const DeepOpt& o, const GemmArgs& a, int cus) {
 }
 
 // The same for the kernel that would run otherwise: rounds of 256 x 256 or 256 x 128
-// tiles on a CU each, or of 128 x 128 tiles two to a CU.
+// tiles on a CU each, or of 128 x 128 tiles two to a CU.  A rougher estimate: it has no
+// term for the rotary epilogue, with which one 3,072-token image's q | k | v takes a
+// fifth longer than it says.
 double plain_time(const GemmArgs& a, int cus) {
   const int i = best_tile(a.M, a.N, nullptr, a.resid != nullptr);
   const TileOpt& o = kTiles[i];
@@ -1247,11 +1264,10 @@ double plain_time(const GemmArgs& a, int cus) {
   return t;
 }
 
-// Tile of the deep kernel when it is the fastest choice by 5% (the estimates'
-// error), else -1.  The residual
-// rows that a micro-batch half leaves after whole rounds of 256 x 256 tiles
-// (`beside`) stay on the persistent residual kernel: that launch runs beside the
-// other half's kernels, which need the CUs' LDS too (CLIP x64: 1%).
+// Tile of the deep kernel when it is the fastest choice by 5% (its own estimate's
+// error), else -1.  The residual rows that a micro-batch half leaves after whole
+// rounds of 256 x 256 tiles (`beside`) stay on the persistent residual kernel: that
+// launch runs beside the other half's kernels, which need the CUs' LDS too (CLIP x64: 1%).
 int best_deep(const GemmArgs& a) {
   if (!tile_rows_fit(a) || (uintptr_t)a.bias % 8 || (a.pos && !a.out_f32)) return -1;
   if (a.beside && a.resid && async_res_ok(a)) return -1;

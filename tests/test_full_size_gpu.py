@@ -10,7 +10,7 @@ micro-batch runs as two concurrent halves on two streams, the GEMMs run the
 large-tile path, including the split of quantised grids into a 256 x 256 head
 launch and a smaller-tile tail launch, and attention runs over the longest
 sequences (9216-token images, 8192-token clips); CLIP x8 runs in one pass on
-the persistent kernels' smaller tiles.
+smaller tiles.
 """
 import numpy as np
 import pytest
@@ -45,8 +45,8 @@ def test_clip_microbatch_64_full_depth():
 
 
 def test_clip_microbatch_8_full_depth():
-    """The first 8 images of the CLIP pool (4616 tokens, one pass: the residual
-    GEMMs on 128 x 128 persistent tiles), full depth."""
+    """The first 8 images of the CLIP pool (4616 tokens, one pass: the
+    O-projection on 128 x 128 persistent tiles, FC2 on 192 x 128 deep ones), full depth."""
     p = C.CLIP_L336
     W = synth.make_weights(p, 0)
     items = synth.make_items(p, 64, 0)[:8]
@@ -64,9 +64,9 @@ def test_clip_microbatch_32_full_depth():
 
 def test_single_requests_full_depth():
     """Micro-batch 1 (the low-load end of the sweep), full depth: one CLIP image
-    (577 tokens) and one audio clip (1500 tokens).  Every GEMM then has no more
-    tiles than there are CUs and runs the latency tiles' deep LDS rings; the
-    batched encodings of the same requests (CLIP x8, audio x8) must match them
+    (577 tokens) and one audio clip (1500 tokens).  Every GEMM of their layers but
+    the clip's FC1 then runs the deep-pipelined kernel, on its four tiles between
+    them; the batched encodings of the same requests (CLIP x8, audio x8) must match them
     bit for bit."""
     for p, pool, r in ((C.CLIP_L336, 64, 3), (C.WHISPER_L, 32, 2)):
         W = synth.make_weights(p, 0)
