@@ -1221,7 +1221,7 @@ namespace {
 // them, is not seen here.  Beside one that leaves 12.5 - 90% of the CUs, one to 16
 // images, one to four audio clips and one video clip were as fast as with the kernels
 // before this one or faster (up to 34%), but for eight images on 70% of them, where
-// FC2's 200 tiles no longer fit one round: 1.5% slower.
+// FC2's 200 tiles no longer fit one round: 0.3 - 1.5% slower.
 struct DeepOpt { const char* name; int bm, bn; double step, slope, e0, e1, r1; };
 constexpr DeepOpt kDeep[4] = {{"gemm_bf16_deep_64x64", 64, 64, 0.165, 0.20, 0.8, 1.2, 1.2},
                               {"gemm_bf16_deep_64x128", 64, 128, 0.237, 0.34, 1.1, 0.8, 2.8},
@@ -1247,8 +1247,8 @@ double deep_time(const DeepOpt& o, const GemmArgs& a, int cus) {
 
 // The same for the kernel that would run otherwise: rounds of 256 x 256 or 256 x 128
 // tiles on a CU each, or of 128 x 128 tiles two to a CU.  A rougher estimate: it has no
-// term for the rotary epilogue, with which one 3,072-token image's q | k | v takes a
-// fifth longer than it says.
+// term for the rotary epilogue, with which one 3,024-token image's q | k | v takes 46
+// us where it says 36.
 double plain_time(const GemmArgs& a, int cus) {
   const int i = best_tile(a.M, a.N, nullptr, a.resid != nullptr);
   const TileOpt& o = kTiles[i];
