@@ -150,6 +150,7 @@ struct GemmArgs {
   int beside;                      // the rows a half leaves after whole rounds of 256 x 256 tiles,
                                    // launched while the other half's kernels run on another stream
   int shared;                      // any launch of a half: the other half's kernels want CUs meanwhile
+                                   // (2: its attention, over long sequences, holds CUs for long)
   // Rotary positions applied in the epilogue of the bf16 q | k | v projection
   // (rope_pos set): output columns [0, rope_cols) are the q and k heads, rope_hd
   // columns each, in interleaved order -- column 2i of a head holds its x_i and

@@ -274,7 +274,7 @@ struct eas_encoder {
   void* qkv_bias = nullptr;  // bf16 rotary ViT: every layer's q | k | v bias, q and k interleaved [layers, 3d]
   int64_t ao_w = 0, hw = 0;  // elements per token of ao and hbuf
   hipStream_t side = nullptr;                          // second half of a split micro-batch
-  bool halves = false;                                 // the call in flight runs as two halves
+  int halves = 0;   // the call in flight runs as two halves (2: with sequences over kLongSeq in both)
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
   hipEvent_t ev_done = nullptr;   // recorded on the caller's stream after each encode call
 
@@ -427,7 +427,7 @@ eas_status gemm(eas_encoder* e, GemmArgs g, hipStream_t s) {
     if (h > 0) {
       const eas_status rc = gemm_launch(e, gemm_rows(g, 0, h), s);
       GemmArgs tail = gemm_rows(g, h, g.M);
-      tail.beside = e->halves;
+      tail.beside = e->halves != 0;
       return rc != EAS_OK ? rc : gemm_launch(e, tail, s);
     }
   }
@@ -743,6 +743,15 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
 // Whisper x8 -0.8% (same-box A/B); below it the halves lose (CLIP x4 -4%,
 // Whisper x4 -7% at a 1024-token threshold).
 constexpr int kSplitTokens = 8192;
+// When both halves hold sequences longer than this, each one's attention has the CUs
+// for so long that the other's GEMMs better run the persistent kernels, whose
+// workgroups find room beside it, than the deep one, whose larger tiles want a CU's
+// whole LDS.  Halves of 4,100 - 4,500 rows, eight layers of 1280, deep against
+// persistent, by the longest sequence of both: 1,500 - 2,500 1.5 - 3% faster, 2,700 and
+// 3,072 1 - 2%, 3,248 equal, 3,600 - 4,480 1.5 - 5% slower (two 4,096-token images 4951
+// -> 4817 us, 4889 before the deep kernel); one half's longest 4,096 - 4,624 and the
+// other's 576 - 2,304, 0 - 4% faster.
+constexpr int kLongSeq = 3328;
 int split_point(const eas_encoder* e, const int32_t* cu, int n, int64_t* in_off, int64_t* out_off) {
   const eas_config& c = e->cfg;
   if (e->prof || !e->side || n < 2 || cu[n] < kSplitTokens) return 0;
@@ -805,13 +814,15 @@ eas_status encode_call(eas_encoder* enc, const void* packed_in, const int32_t* c
     for (int r = 0; r <= n_seqs - k; ++r) cub[r] = cu_seqlens[k + r] - cu_seqlens[k];
     if (hipEventRecord(enc->ev_fork, s) != hipSuccess || hipStreamWaitEvent(enc->side, enc->ev_fork, 0) != hipSuccess)
       return fail(enc, EAS_ERR_HIP, "stream fork failed");
-    enc->halves = true;
+    int longest[2] = {0, 0};
+    for (int r = 0; r < n_seqs; ++r) longest[r >= k] = std::max(longest[r >= k], cu_seqlens[r + 1] - cu_seqlens[r]);
+    enc->halves = std::min(longest[0], longest[1]) > kLongSeq ? 2 : 1;
     rc = encode_part(enc, enc->rows_from(0), packed_in, cu_seqlens, grid_thw, k, weights, out_embeddings, s);
     if (rc == EAS_OK)
       rc = encode_part(enc, enc->rows_from(cu_seqlens[k]), static_cast<const char*>(packed_in) + in_off, cub.data(),
                        grid_thw ? grid_thw + 3 * k : nullptr, n_seqs - k, weights,
                        static_cast<char*>(out_embeddings) + out_off, enc->side);
-    enc->halves = false;
+    enc->halves = 0;
     // joined even after an error: the caller's stream never runs ahead of the side stream
     const bool joined = hipEventRecord(enc->ev_join, enc->side) == hipSuccess &&
                         hipStreamWaitEvent(s, enc->ev_join, 0) == hipSuccess;

@@ -1237,6 +1237,8 @@ double deep_time(const DeepOpt& o, const GemmArgs& a, int cus) {
   // such a half's tail leaves the other half a quarter of the CUs (24 images, a tail
   // of 216 tiles: 1.5% slower; 16 images, 160 tiles: 1.8% faster)
   if (a.beside && 4 * tiles > 3L * cus) return 1e300;
+  // beside attention over long sequences the larger tiles wait for whole CUs; a tail's few do not
+  if (a.shared == 2 && !a.beside) return 1e300;
   double t = kDispatchUs;
   for (long left = tiles; left > 0; left -= cus) {
     const double load = (double)(left < cus ? left : cus) / cus;
