@@ -450,20 +450,24 @@ int attention_dma_q_tile(int hd, const int* cu, int n) {
   return s256 * 100 <= s128 * 102 ? 256 : 128;
 }
 
-// Of a span of `bytes` weight bytes, how many the launch of `blocks` attention blocks
-// reads ahead: all or none.  The paced reads of a long span outlast the attention
-// blocks (1,731 rows, 100 MB a layer: 20 -> 42 us a launch), and behind a launch that
-// fills the chip they take their own time while the GEMMs that follow are long enough
-// to wait for nothing.  Eight layers, read against not read: 39 MB (one to eight images,
-// hidden 1280) 1-11% faster, 57 MB (1536) 2% slower to 5% faster, 77 MB (1664) 4% slower
-// to 1% faster, 100 MB (2048) 2-8% slower; four layers of 300 MB 2-19% slower, and
-// slower than without any read-ahead before it (two images 2202 -> 2394 us; now 2049).
-// A Qwen-style merger's span, 118 MB once a call, whose GEMMs have a quarter of the
-// rows: images under 1,000 tokens 1-3% slower with it, 5,776 tokens, which fill the chip,
-// 0.9% faster.
-long attention_dma_ahead(int blocks, int qt, long bytes, bool merger) {
-  const long most = merger && fills_chip(blocks, qt) ? 128l << 20 : 64l << 20;
-  return bytes <= most ? bytes : 0;
+// Of a span of `bytes` weight bytes, how many an attention launch over sequences of up
+// to `longest` tokens reads ahead: all or none.  The paced reads of a long span outlast
+// a short launch (1,731 rows of three images, 100 MB a layer: 20 -> 42 us a launch), and
+// behind a launch that fills the chip they take their own time while the GEMMs that
+// follow wait for little.  Spans over 64 MiB are read when the launch walks a key tile
+// for each 4 MiB, and never over 128 MiB (half the cache).  Read against not read, eight
+// layers, one to eight images of 577 tokens: 39 MB a layer (hidden 1280) 1-11% faster, 57
+// MB (1536) 2% slower to 5% faster, 77 MB (1664) 4% slower to 1% faster, 100 MB (2048) 2-8%
+// slower; four layers of 300 MB 2-19% slower, and slower than without any read-ahead
+// before it (two images 2202 -> 2394 us; now 2049).  73 MB a layer (hidden 1600, mlp
+// 8192), one image: 256 - 1,024 tokens 4-14% slower, 1,536 (24 key tiles) - 2,688 3-5%
+// faster, 4,096 3% faster.  A Qwen-style merger's span, 118 MB once a call, two layers:
+// up to 1,764 tokens 1-14% slower, 2,024 (32 key tiles) - 3,136 1-7% faster, 3,600 - 4,488
+// within 1%.
+long attention_dma_ahead(int longest, long bytes) {
+  constexpr long kMiB = 1l << 20;
+  const long cover = (longest + 63) / 64 * 4 * kMiB;
+  return bytes <= 64 * kMiB || (bytes <= cover && bytes <= 128 * kMiB) ? bytes : 0;
 }
 
 bool attention_dma_supported(const AttnArgs& a, int N) {

@@ -234,7 +234,7 @@ hipError_t launch_attention_bf16(const AttnArgs& a, const AttnWork& w, int total
 // the sequences of a micro-batch (cu: n + 1 prefix sums)
 bool attention_dma_supported(const AttnArgs& a, int N);
 int attention_dma_q_tile(int hd, const int* cu, int n);
-long attention_dma_ahead(int blocks, int qt, long bytes, bool merger);
+long attention_dma_ahead(int longest, long bytes);
 hipError_t launch_attention_bf16_dma(const AttnArgs& a, const AttnWork& w, int total_tiles, hipStream_t s,
                                      const char** kname);
 hipError_t launch_attention_f32(const AttnArgs& a, const AttnWork& w, int total_tiles, hipStream_t s,

@@ -676,7 +676,7 @@ eas_status encode_part(eas_encoder* enc, const Workspace& ws, const void* packed
                          : c.merge == 2   ? enc->layout.off("m2.b")
                                           : enc->layout.off(p + "fc2.b");
       aa.ahead = static_cast<const char*>(weights) + from;
-      aa.ahead_bytes = attention_dma_ahead(tiles * H, qt, (long)(to - from), c.merge == 2 && l + 1 == c.layers);
+      aa.ahead_bytes = attention_dma_ahead(cu_seqlens[ord[0] + 1] - cu_seqlens[ord[0]], (long)(to - from));
     }
     // the record's bytes and time include the weights read ahead
     EAS_TRY(run(enc, s, attn_flops, (double)N * 4 * d * el + (double)aa.ahead_bytes, [&](const char** kn) {

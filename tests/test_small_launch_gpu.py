@@ -165,7 +165,7 @@ def test_pack_strips_of_large_launches(merge):
         enc.close()
 
 
-def _attention_bytes(p, n, offset=0):
+def _attention_bytes(p, n, offset=0, side=None):
     """Recorded bytes of all attention launches of one call, less the activations', and
     the weight spans between each layer's attention and the next (or the call's end)."""
     import torch
@@ -177,7 +177,7 @@ def _attention_bytes(p, n, offset=0):
     spans = [off["layers.%d.qkv.b" % (i + 1)] - off["layers.%d.o.w" % i] for i in range(p["layers"] - 1)]
     spans.append(off["m2.b" if p["merge"] == 2 else last + "fc2.b"] - off[last + "o.w"])
     enc = eas.Encoder(p, 1 << 15)
-    side = 336 if p["kind"] == C.KIND_VIT_CLS_ABS else 280
+    side = side or (336 if p["kind"] == C.KIND_VIT_CLS_ABS else 280)
     items = [torch.rand((p["temporal_patch"], 3, side, side), device="cuda") for _ in range(n)]
     packed, cu, grid = enc.pack_microbatch(items)
     enc.profile_read()
@@ -204,18 +204,21 @@ def test_attention_records_the_weights_it_reads_ahead(preset):
     assert _attention_bytes(p, 1)[0] == 0
 
 
-def test_attention_reads_no_long_spans_ahead():
-    """Weight spans over 64 MiB (hidden 2048: 101 and 76 MB here) are left, in small
-    launches and in those that fill the chip; the merger's (118 MB) is read only by the
-    latter."""
+def test_attention_reads_long_spans_ahead_over_long_sequences_only():
+    """Weight spans over 64 MiB (hidden 2048: 101 and 76 MB; the merger's: 118 MB) are left
+    unless the launch walks a key tile of 64 for each 4 MiB, whatever its blocks; spans
+    over 128 MiB always."""
     p = dict(C.with_layers(C.CLIP_L336, 2), name="clip_w2048", hidden=2048, heads=32, mlp=8192, out_dim=2048)
-    for n in (1, 8):
+    for n in (1, 8):   # 10 key tiles
         ahead, spans = _attention_bytes(p, n)
         assert min(spans) > 64 << 20 and ahead == 0
     p = C.with_layers(C.QWEN_IMAGE, 2)
-    ahead, spans = _attention_bytes(p, 1)
-    assert ahead == spans[0] <= 64 << 20 < spans[1]
-    assert _attention_bytes(p, 14)[0] == sum(spans)
+    for n, side, merger in ((1, 280, 0), (14, 280, 0), (1, 588, 0), (1, 616, 1)):   # 7, 7, 28 and 31 key tiles
+        ahead, spans = _attention_bytes(p, n, side=side)
+        assert spans[0] <= 64 << 20 < spans[1] and ahead == spans[0] + merger * spans[1], (n, side)
+    p = dict(p, name="qwen_m32768", mlp=32768)   # 167 MB a layer
+    ahead, spans = _attention_bytes(p, 1, side=1344)
+    assert min(spans) > 128 << 20 and ahead == 0
 
 
 def test_attention_reads_nothing_ahead_of_unaligned_weights():
